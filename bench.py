@@ -138,6 +138,14 @@ def mixed_batch(H, torch, prec, steps):
             "sigma_fb": {str(n): r["sigma_fb"] for n, r in zip(ns, res)}}
 
 
+def kernel_name(prec, n, shape):
+    """The amplitude kernel of a shape (prefix_sets = 5: helicities over lanes) as profiles name it."""
+    real = "float" if prec == "fp32" else "double"
+    if shape[7] == 5:
+        return f"me2_lanes_kernel<{real},{n}>"
+    return "me2_kernel<{},{},{}>".format(real, n, ",".join(str(v) for v in shape))
+
+
 def per_n(H, torch, tune, ns=range(2, 9)):
     """Amplitude kernel alone (heget_me2_device) for n = 2..8 on device-generated
     points (sqrt(shat) = 1 TeV, seed 11, no cuts so every point is a valid input),
@@ -354,9 +362,7 @@ def config_n8(H, torch, wl, reps):
         out[name] = {"points_per_s": r["n_acc"] / dt, "ms_per_pass": dt * 1e3, "points_evaluated": r["n_acc"],
                      "sigma_fb": r["sigma_fb"], "sigma_err_fb": r["err_fb"],
                      "roofline": {"bound": "alu", "achieved": ach, "peak": peak_of(name), "unit": "TFLOP/s",
-                                  "frac": ach / peak_of(name), "kernel": "me2_kernel<{},8,{}>".format(
-                                      "float" if name == "fp32" else "double",
-                                      ",".join(str(v) for v in shape)),
+                                  "frac": ach / peak_of(name), "kernel": kernel_name(name, 8, shape),
                                   "kernel_ms": kms, "flops_per_point": f}}
         print(f"bench: n=8 workload {name} {dt * 1e3:.1f} ms/pass, kernel {kms:.1f} ms, "
               f"{r['n_acc'] / dt:.3e} pts/s, frac {ach / peak_of(name):.2f}", file=sys.stderr, flush=True)
@@ -489,7 +495,7 @@ def main():
     peak = H.valu_peak()
     print(f"bench: FMA probe FP32 {peak['fp32_tflops']:.1f}, FP64 {peak['fp64_tflops']:.1f} TFLOP/s",
           file=sys.stderr, flush=True)
-    kname = "me2_kernel<float,{},{}>".format(n, ",".join(str(v) for v in shape32))
+    kname = kernel_name("fp32", n, shape32)
     from paper_0908_4403_amd.profiling import read_traffic
     traffic_md = os.path.join(ROOT, "profiles", f"me2_kernel_{args.workload}_hbm_traffic.md")
     traffic = read_traffic(traffic_md, kname)

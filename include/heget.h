@@ -164,7 +164,8 @@ heget_status heget_xsec_device(int n, const heget_config *cfg, heget_result *d_o
  * workspace that the library holds in a static device array, one per device,
  * kept until the process ends.  The call allocates nothing (no hipMalloc,
  * hipFree or pinned host memory).  A configuration whose buffers exceed the
- * workspace -- about 32 (n + 2) + 14 bytes per point, e.g. 3.2e5 points at
+ * workspace -- about 32 (n + 2) + 14 bytes per point and 8 more for an
+ * amplitude pass that writes |M|^2 (n >= 6, small calls), e.g. 3.2e5 points at
  * n = 4 or 2.0e5 at n = 8 -- returns HEGET_ERR_RANGE before anything is
  * enqueued.  Every call on one device shares that device's workspace: calls
  * that overlap on the device (concurrent streams, or a captured graph
@@ -299,7 +300,12 @@ heget_status heget_timing_read(double *me2_ms, int64_t *me2_launches, int reset)
  *                        momentum part of the nodes formed once per point;
  *                        3: as 2 with it formed per helicity walk (fewer
  *                        values held, for n >= 7); 4: as 3 with the v-bar-end
- *                        currents of K - 1 photons held in LDS */
+ *                        currents of K - 1 photons held in LDS;
+ *                        5 (n = 6, 7, 8; the default there): no walk of one lane
+ *                        per point -- the same meeting in the middle with the
+ *                        helicities of a point spread over 2^(n-2) lanes of a
+ *                        wave and every subset current formed once for the
+ *                        helicities it depends on (helicities_per_walk = 2^n) */
 typedef struct {
     int32_t unrolled, helicities_per_walk, closing, waves_per_block, prefetch, waves_per_simd,
         points_per_lane, prefix_sets;
@@ -325,9 +331,11 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
 heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape *chosen,
                             double *ms);
 
-/* The compiled shapes for (n, prec), the one in use first, into shapes[i]
- * for i < max (shapes may be NULL when max = 0); *count receives how many
- * exist. */
+/* The compiled walk shapes (prefix_sets <= 4) for (n, prec), the one in use
+ * first, into shapes[i] for i < max (shapes may be NULL when max = 0); *count
+ * receives how many exist.  The kernel of prefix_sets = 5 is not among them:
+ * heget_me2_flops names it where it is in use, and heget_set_kernel_shape
+ * takes its shape. */
 heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *shapes, int *count);
 
 /* Use a compiled shape for (n, prec) from now on in this process; NULL

@@ -299,22 +299,42 @@ int plan_chunks(const heget::Me2Variant &v, int64_t points_expected)
 // Shape chosen by the autotuner (or loaded from the tuning cache) per (prec, n).
 const heget::Me2Variant *g_tuned[2][9] = {};
 
+// The kernel without a chosen shape: helicities over the lanes of a wave where
+// it is compiled (n >= 6), else the first walk shape.  From n = 6 a lane holds
+// too few helicities to share the currents (points/s, walk against lanes, at
+// 1, 517 and about 1e5 points alike: n = 6 FP32 3.3e8 against 6.2e8, FP64
+// 9.7e7 against 3.6e8; n = 8 1.2e6 against 3.8e7 in FP64); at n = 5 the walk
+// holds eight of 32 in registers and wins (FP32 1.24e9 against 1.07e9, FP64
+// 6.1e8 against 5.6e8 at 200 003 points).
+const heget::Me2Variant *default_variant(int prec, int n)
+{
+    const heget::Me2Variant *l = heget::me2_lanes(prec, n);
+    return l ? l : heget::me2_default(prec, n);
+}
+
 const heget::Me2Variant *pick_variant(int prec, int n)
 {
     if (prec >= 0 && prec < 2 && n >= 2 && n <= 8 && g_tuned[prec][n]) return g_tuned[prec][n];
-    return heget::me2_default(prec, n);
+    return default_variant(prec, n);
 }
+
+// The amplitude kernel writes |M|^2 per point and the weighted sums follow in
+// a pass of their own (the walk kernels of one chunk take them in their epilogue).
+bool sums_apart(const heget::Me2Variant &v, int nchunks) { return nchunks > 1 || v.ps == heget::kLanesPs; }
 
 const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, int wpb, int pf, int wpe,
                                       int ppl, int ps)
 {
+    auto is = [&](const heget::Me2Variant &v) {
+        return v.prec == prec && v.n == n && v.mb == mb && v.h == h && v.cl == cl && v.wpb == wpb &&
+               v.pf == pf && v.wpe == wpe && v.ppl == ppl && v.ps == ps;
+    };
     int cnt = 0;
     const heget::Me2Variant *v = heget::me2_variants(&cnt);
     for (int i = 0; i < cnt; ++i)
-        if (v[i].prec == prec && v[i].n == n && v[i].mb == mb && v[i].h == h && v[i].cl == cl &&
-            v[i].wpb == wpb && v[i].pf == pf && v[i].wpe == wpe && v[i].ppl == ppl && v[i].ps == ps)
-            return &v[i];
-    return nullptr;
+        if (is(v[i])) return &v[i];
+    const heget::Me2Variant *l = heget::me2_lanes(prec, n);
+    return l && is(*l) ? l : nullptr;
 }
 
 heget_shape shape_of(const heget::Me2Variant &v)
@@ -637,6 +657,7 @@ struct McBufs {
     double *wout;   // per-survivor weights (histograms), or nullptr
     int64_t *d_count;
     int nchunks;
+    bool apart;     // the weighted sums follow the amplitude pass (sums_apart)
 };
 
 // Status of a finished Monte-Carlo call from its device flags.
@@ -683,13 +704,13 @@ heget_status enqueue_generation(int n, const heget_config &c, const McBufs &b, h
 }
 
 // Weighted sums after the amplitude pass: the weighted chunk sums when the
-// amplitude pass wrote |M|^2 (split walks, or `weighted_in_me2` false), then
-// the fixed-order reduction into b.res (and the result record if given).
+// amplitude pass wrote |M|^2, then the fixed-order reduction into b.res (and
+// the result record if given).
 heget_status enqueue_reduction(const heget_config &c, const McBufs &b, unsigned *flags, void *record,
-                               hipStream_t s, bool weighted_in_me2 = true)
+                               hipStream_t s)
 {
     const int64_t np = c.npoints;
-    if (b.nchunks > 1 || !weighted_in_me2)
+    if (b.apart)
         HG_HIP(heget::launch_sum_chunks(b.part, b.nchunks, np, b.d_count, np, nullptr, b.index,
                                         b.wfac, b.partials, b.wout, flags, s));
     HG_HIP(heget::launch_final(b.partials, b.d_count, np, b.res, record, s));
@@ -702,7 +723,7 @@ heget_status enqueue_reduction(const heget_config &c, const McBufs &b, unsigned 
 heget::Me2Args mc_me2_args(int n, const heget_config &c, const McBufs &b, unsigned *flags)
 {
     const double coef = me2_coef(n, c.alpha, c.charge) * (b.hel ? double(1 << n) : 1.0);
-    const bool epi = b.nchunks == 1;
+    const bool epi = !b.apart;
     return heget::Me2Args{b.mom,      c.npoints,  b.index,  b.hel,  b.d_count,
                           c.npoints,  b.nchunks,  coef,     b.part, c.npoints,
                           b.wfac,     epi ? b.partials : nullptr, epi ? b.wout : nullptr, flags};
@@ -737,6 +758,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     const int64_t nb = (np + 255) / 256;
     McBufs b{};
     b.nchunks = sampled ? 1 : plan_chunks(*v, np / 2);
+    b.apart = sums_apart(*v, b.nchunks);
     unsigned *flags;
     HG_TRY(scratch_bind(s));
     HG_TRY(scratch_t<double>(S_MOM, size_t(n + 2) * 4 * size_t(np), &b.mom));
@@ -763,7 +785,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
         HG_TRY(scratch_t<double>(S_HIST, size_t(hist->nbins) + 2, &d_hist));
     }
     b.part = nullptr;
-    if (b.nchunks > 1) HG_TRY(scratch_t<double>(S_PART, size_t(b.nchunks) * size_t(np), &b.part));
+    if (b.apart) HG_TRY(scratch_t<double>(S_PART, size_t(b.nchunks) * size_t(np), &b.part));
     // one spare tile slot: two-points-per-lane shapes write a zero sum there
     HG_TRY(scratch_t<double>(S_PARTIALS, size_t(3) * size_t((np + 63) / 64 + 1), &b.partials));
     HG_TRY(scratch_t<double>(S_RES, 8, &b.res));
@@ -857,8 +879,8 @@ void carve_batch(Arena &ar, int ncfg, const int *n, const heget_config *cfgs, in
         b.wout = nullptr;
         b.d_count = ar.take<int64_t>(1);
         // the persistent kernel always writes |M|^2 per chunk
-        const bool need_part = b.nchunks > 1 || schedule == 1;
-        b.part = need_part ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
+        b.apart = schedule == 1 || sums_apart(*pick_variant(cfgs[s].prec, n[s]), b.nchunks);
+        b.part = b.apart ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
         b.partials = ar.take<double>(size_t(3) * size_t((np + 63) / 64 + 1));  // + spare tile slot
         b.res = ar.take<double>(4);
     }
@@ -922,7 +944,7 @@ heget_status batch_enqueue(int ncfg, const int *n, const heget_config *cfgs, Sli
     const int grid = cus * heget::me2_batch_blocks_per_cu(cfgs[0].prec);
     HG_HIP(heget::launch_me2_batch(cfgs[0].prec, bd, grid, s));
     for (int i = 0; i < ncfg; ++i) {
-        HG_TRY(enqueue_reduction(cfgs[i], sb[i].b, flags, nullptr, s, false));
+        HG_TRY(enqueue_reduction(cfgs[i], sb[i].b, flags, nullptr, s));
         HG_HIP(hipMemcpyAsync(staged + 4 * i, sb[i].b.res, 4 * sizeof(double),
                               hipMemcpyDeviceToHost, s));
     }
@@ -1030,6 +1052,7 @@ void carve_static(int n, const heget_config &c, const heget::Me2Variant &v, Aren
     const bool sampled = c.helicity_sampling != 0;
     b = McBufs{};
     b.nchunks = sampled ? 1 : plan_chunks(v, np / 2);
+    b.apart = sums_apart(v, b.nchunks);
     *flags = ar.take<unsigned>(1);
     b.d_count = ar.take<int64_t>(1);
     b.res = ar.take<double>(8);
@@ -1040,7 +1063,7 @@ void carve_static(int n, const heget_config &c, const heget::Me2Variant &v, Aren
     b.index = ar.take<int32_t>(size_t(np));
     b.hel = sampled ? ar.take<uint16_t>(size_t(np)) : nullptr;
     b.wout = nullptr;
-    b.part = b.nchunks > 1 ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
+    b.part = b.apart ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
     b.partials = ar.take<double>(size_t(3) * size_t((np + 63) / 64 + 1));  // + spare tile slot
 }
 
@@ -1581,10 +1604,11 @@ heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape
     HG_HIP(hipEventCreate(&e1));
     int cnt = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
+    const heget::Me2Variant *lanes = heget::me2_lanes(prec, n);
     const heget::Me2Variant *best = nullptr;
     double best_ms = 0.0;
-    for (int i = 0; i < cnt; ++i) {
-        const heget::Me2Variant &v = all[i];
+    for (int i = lanes ? -1 : 0; i < cnt; ++i) {
+        const heget::Me2Variant &v = i < 0 ? *lanes : all[i];
         if (v.prec != prec || v.n != n) continue;
         const int nchunks = plan_chunks(v, npoints);
         double *out = nullptr;
@@ -1646,6 +1670,7 @@ heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *s
     int cnt = 0, k = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
     const heget::Me2Variant *cur = pick_variant(prec, n);
+    if (cur && cur->ps == heget::kLanesPs) cur = heget::me2_default(prec, n);  // no walk shape
     if (cur) {  // the shape in use first
         if (k < max) shapes[k] = shape_of(*cur);
         ++k;

@@ -25,12 +25,17 @@ struct Me2Variant {
     int ps;     // 1: top levels walked by prefix sets (currents summed over their orderings);
                 // 2-4: meet in the middle (2: momenta once per point, 3: per walk,
                 // 4: per walk with the held v-bar-end currents in LDS)
+                // kLanesPs: helicities over the lanes of a wave (me2_lanes.hpp)
     const void *func;  // kernel symbol
 };
 
-// All compiled variants (static table) and the default choice per (prec, n).
+constexpr int kLanesPs = 5;
+
+// All compiled walk variants (one lane per point; static table) and the first one per (prec, n).
 const Me2Variant *me2_variants(int *count);
 const Me2Variant *me2_default(int prec, int n);
+// The kernel with a point's helicities over the lanes of a wave for (prec, n), or nullptr.
+const Me2Variant *me2_lanes(int prec, int n);
 // The helicity-sampling kernel (h = 0) for (prec, n).
 const Me2Variant *me2_sampled(int prec, int n);
 

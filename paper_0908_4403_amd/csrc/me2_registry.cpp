@@ -18,6 +18,8 @@ extern const int kShapesF32LoCount, kShapesF32MidCount, kShapesF32Meet7Count, kS
 extern const int kShapesF64LoCount, kShapesF64MidCount, kShapesF64HiCount;
 extern const Me2Variant kShapesSampled[], kShapesSampledMeet8[];
 extern const int kShapesSampledCount, kShapesSampledMeet8Count;
+extern const Me2Variant kShapesLanes[];
+extern const int kShapesLanesCount;
 
 static const std::vector<Me2Variant> &all_variants()
 {
@@ -47,6 +49,13 @@ const Me2Variant *me2_default(int prec, int n)
 {
     for (const Me2Variant &v : all_variants())
         if (v.prec == prec && v.n == n) return &v;
+    return nullptr;
+}
+
+const Me2Variant *me2_lanes(int prec, int n)
+{
+    for (int i = 0; i < kShapesLanesCount; ++i)
+        if (kShapesLanes[i].prec == prec && kShapesLanes[i].n == n) return &kShapesLanes[i];
     return nullptr;
 }
 
@@ -81,7 +90,12 @@ static int64_t resident_blocks(const Me2Variant &v)
 hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream)
 {
     const int64_t ntiles = (a.count + 63) / 64;
-    const int64_t items = (ntiles + v.ppl - 1) / v.ppl * a.nchunks;
+    int64_t items = (ntiles + v.ppl - 1) / v.ppl * a.nchunks;
+    if (v.ps == kLanesPs) {  // 2^(8 - n) points per wave, |M|^2 of each to out
+        const int64_t per = int64_t(1) << (8 - v.n);
+        if (a.nchunks != 1 || a.partials || !a.out) return hipErrorInvalidValue;
+        items = (a.count + per - 1) / per;
+    }
     if (items == 0) return hipSuccess;
     int64_t blocks = (items + v.wpb - 1) / v.wpb;
     if (v.pf) {

@@ -268,3 +268,32 @@ def test_golden_writer_imports_only_the_oracle():
     assert "paper_0908_4403_amd" not in src
     wl = open(os.path.join(ROOT, "workloads.py")).read()
     assert not re.search(r"^\s*(import|from)\s", wl, flags=re.M)
+
+
+def test_lanes_kernel_is_the_default_from_n6_and_no_walk_shape():
+    """Without a chosen shape n = 6, 7, 8 run the kernel that spreads the
+    helicities over lanes: its count is the fully shared one (one walk of all
+    2^n helicities), and the list of walk shapes does not name it."""
+    import math
+    import paper_0908_4403_amd as H
+    for n in range(2, 9):
+        for prec in (H.FP32, H.FP64):
+            f, shape = H.me2_flops(n, prec)
+            assert (shape[7] == 5) == (n >= 6), (n, shape)
+            walks = H.kernel_shapes(n, prec)
+            assert all(s[7] <= 4 for s in walks)
+            if n < 6:
+                continue
+            assert len(set(walks)) == len(walks) and shape[:2] == (n, 1 << n)
+            K = (n + 1) // 2
+            node = lambda m: 14 + 2 ** m * (11 if m == 1 else 36 + 20 * (m - 1))
+            want = sum(math.comb(n, m) * node(m) for m in [*range(1, K + 1), *range(1, n - K)])
+            want += math.comb(n, K) * ((16 + 20 * (n - K - 1)) * 2 ** (n - K) + 16 * 2 ** n)
+            assert f == want + 4 * n + 4 * 2 ** n, (n, f, want)
+            try:
+                H.set_kernel_shape(n, prec, walks[0])
+                assert H.me2_flops(n, prec)[1] == walks[0] and H.kernel_shapes(n, prec) == walks
+                H.set_kernel_shape(n, prec, shape)
+                assert H.me2_flops(n, prec)[1] == shape
+            finally:
+                H.set_kernel_shape(n, prec, None)
