@@ -188,7 +188,7 @@ def per_n(H, torch, tune, ns=range(2, 9)):
               f"({row['fp32']['frac']:.2f}), FP64 {row['fp64']['points_per_s']:.3e} "
               f"({row['fp64']['frac']:.2f})", file=sys.stderr, flush=True)
         if n <= 5:
-            # the general-frame evaluator composed from the HELAS library, same points
+            # the general-frame evaluator, same points
             frame = {}
             for prec, name in ((H.FP32, "fp32"), (H.FP64, "fp64")):
                 fn = min(npts, 1 << 18)

@@ -384,11 +384,13 @@ heget_status heget_helas_device(int func, int64_t count, const double *d_in, dou
                                 heget_prec prec, heget_stream stream);
 
 /* Helicity-summed |M|^2 of u(p1) ubar(p2) -> n photons (2 <= n <= 5) for
- * massless momenta in any frame, composed from the library functions
- * (ixxxx0, oxxxx0, vxxxx0, fvoxx0 over all n! orderings, iovxxx).  Layouts
- * as heget_me2 (momenta[npoints][n+2][4], host); the couplings of
- * heget_set_couplings.  Every photon needs E > 0.  Equal to heget_me2 in the
- * frame where it applies.  HEGET_ERR_RANGE for n outside 2..5. */
+ * massless momenta in any frame (p1 + p2 = sum of the photons): the subset
+ * currents of heget_me2 in the frame where u and ubar lie on the z axis,
+ * whose light-cone momenta are formed as products of the Weyl spinors of
+ * ixxxx0.  Layouts as heget_me2 (momenta[npoints][n+2][4], host); the
+ * couplings of heget_set_couplings.  Every photon needs E > 0.  Equal to
+ * heget_me2 in the frame where it applies.  HEGET_ERR_RANGE for n outside
+ * 2..5. */
 heget_status heget_me2_frame(int n, int64_t npoints, const double *momenta, double *out_me2,
                              heget_prec prec);
 
