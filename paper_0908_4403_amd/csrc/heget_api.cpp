@@ -82,7 +82,8 @@ struct State {
     Scratch ctx[kContexts];           // ctx[0] belongs to `stream`
     Scratch *cur = nullptr;           // context of the call in progress
     uint64_t tick = 0;
-    double *pinned = nullptr;         // staging ring for results (kRing slots of 8 doubles)
+    double *pinned = nullptr;         // staging ring for results (kRing slots of kStaged doubles)
+    double *pinned_hist = nullptr;    // bins of heget_xsec_hist (first such call)
     std::atomic<unsigned> ring{0};
     // side streams and fork/join events of the parallel batch schedule
     hipStream_t side[8] = {};
@@ -97,10 +98,13 @@ struct State {
 };
 State g;
 constexpr int kRing = 256;
+// Result of one configuration in pinned memory, written by the final reduction
+// itself: sum, compensation, sum of squares, survivors, status flags.
+constexpr int kStaged = 8;
 
 enum Slot {
     S_MOM, S_WFAC, S_FLAG, S_BCOUNT, S_COUNT, S_INDEX, S_PART, S_PARTIALS, S_RES, S_FLAGS,
-    S_OUT, S_BATCH, S_HEL, S_WOUT, S_BINS, S_HIST, S_EVW, S_EVY, S_EVH, S_NSLOTS
+    S_OUT, S_BATCH, S_HEL, S_WOUT, S_BINS, S_EVW, S_EVY, S_EVH, S_NSLOTS
 };
 
 // Captured mixed-n batches, keyed by their configuration; replayed on repeat calls.
@@ -108,7 +112,7 @@ struct BatchGraph {
     std::string key;
     hipGraphExec_t exec = nullptr;  // the schedule in use for this key
     hipGraphExec_t other = nullptr; // kept only while "auto" compares the two
-    double *staged = nullptr;       // pinned: 4 doubles per slice + flags
+    double *staged = nullptr;       // pinned: kStaged doubles per slice
     int schedule = 0;               // 1 persistent, 2 branches
 };
 std::vector<BatchGraph> g_graphs;
@@ -137,7 +141,7 @@ heget_status ensure_device()
                                           " devices)");
     HG_HIP(hipGetDevice(&g.device));
     HG_HIP(hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking));
-    HG_HIP(hipHostMalloc(reinterpret_cast<void **>(&g.pinned), sizeof(double) * 8 * kRing,
+    HG_HIP(hipHostMalloc(reinterpret_cast<void **>(&g.pinned), sizeof(double) * kStaged * kRing,
                          hipHostMallocDefault));
     for (Scratch &c : g.ctx) {
         c.buf.assign(S_NSLOTS, nullptr);
@@ -705,15 +709,15 @@ heget_status enqueue_generation(int n, const heget_config &c, const McBufs &b, h
 
 // Weighted sums after the amplitude pass: the weighted chunk sums when the
 // amplitude pass wrote |M|^2, then the fixed-order reduction into b.res (and
-// the result record if given).
+// the result record or the pinned result, if given).
 heget_status enqueue_reduction(const heget_config &c, const McBufs &b, unsigned *flags, void *record,
-                               hipStream_t s)
+                               double *staged, hipStream_t s)
 {
     const int64_t np = c.npoints;
     if (b.apart)
         HG_HIP(heget::launch_sum_chunks(b.part, b.nchunks, np, b.d_count, np, nullptr, b.index,
                                         b.wfac, b.partials, b.wout, flags, s));
-    HG_HIP(heget::launch_final(b.partials, b.d_count, np, b.res, record, s));
+    HG_HIP(heget::launch_final(b.partials, b.d_count, np, b.res, record, flags, staged, s));
     return HEGET_OK;
 }
 
@@ -733,7 +737,7 @@ heget::Me2Args mc_me2_args(int n, const heget_config &c, const McBufs &b, unsign
 struct HistReq {
     int observable, nbins;
     double lo, hi;
-    double *host;  // [nbins + 2], written by a copy enqueued on the stream
+    double *host;  // [nbins + 2], pinned, written by the last kernel
 };
 
 // Per-event records to copy out beside the cross section (heget_xsec_events):
@@ -744,9 +748,12 @@ struct EventReq {
 };
 
 // Enqueue the whole path.  The result goes to d_out (device-writable, filled by
-// a kernel) when given, else to *out through the pinned ring and a host callback.
+// a kernel) when given, else to a slot of the pinned ring: to *out by a host
+// callback when `out` is given (asynchronous calls), and the slot's address to
+// *staged_out (calls that wait for the stream and read it themselves: no copy
+// and no callback, 60 of the 85 us of a 16384-point n = 2 call).
 heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heget_result *d_out,
-                          hipStream_t s, unsigned **flags_out, const HistReq *hist = nullptr,
+                          hipStream_t s, double **staged_out, const HistReq *hist = nullptr,
                           const EventReq *ev = nullptr)
 {
     const int64_t np = cfg->npoints;
@@ -771,7 +778,6 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     if (sampled) HG_TRY(scratch_t<uint16_t>(S_HEL, size_t(np), &b.hel));
     b.wout = nullptr;
     unsigned long long *bins = nullptr;
-    double *d_hist = nullptr;
     if (hist || ev) HG_TRY(scratch_t<double>(S_WOUT, size_t(np), &b.wout));
     double *ev_w = nullptr, *ev_y = nullptr;
     uint16_t *ev_h = nullptr;
@@ -780,10 +786,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
         if (ev->rapidity) HG_TRY(scratch_t<double>(S_EVY, size_t(np), &ev_y));
         if (ev->helicity) HG_TRY(scratch_t<uint16_t>(S_EVH, size_t(np), &ev_h));
     }
-    if (hist) {
-        HG_TRY(scratch_t<unsigned long long>(S_BINS, size_t(hist->nbins) + 2, &bins));
-        HG_TRY(scratch_t<double>(S_HIST, size_t(hist->nbins) + 2, &d_hist));
-    }
+    if (hist) HG_TRY(scratch_t<unsigned long long>(S_BINS, size_t(hist->nbins) + 2, &bins));
     b.part = nullptr;
     if (b.apart) HG_TRY(scratch_t<double>(S_PART, size_t(b.nchunks) * size_t(np), &b.part));
     // one spare tile slot: two-points-per-lane shapes write a zero sum there
@@ -793,14 +796,14 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
 
     HG_TRY(enqueue_generation(n, *cfg, b, s, flags));  // also clears flags
     HG_TRY(launch_me2_timed(*v, mc_me2_args(n, *cfg, b, flags), s));
-    HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, s));
+    double *staged = d_out ? nullptr : g.pinned + kStaged * (g.ring.fetch_add(1) % kRing);
+    if (staged_out) *staged_out = staged;
+    HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, staged, s));
     if (hist) {
         HG_HIP(heget::launch_zero_u32(reinterpret_cast<unsigned *>(bins), 2 * (hist->nbins + 2), s));
         HG_HIP(heget::launch_hist(n, b.mom, np, b.index, b.wout, b.d_count, np, b.res,
                                   hist->observable, hist->nbins, hist->lo, hist->hi, bins, s));
-        HG_HIP(heget::launch_hist_finish(bins, hist->nbins, b.res, np, d_hist, s));
-        HG_HIP(hipMemcpyAsync(hist->host, d_hist, sizeof(double) * size_t(hist->nbins + 2),
-                              hipMemcpyDeviceToHost, s));
+        HG_HIP(heget::launch_hist_finish(bins, hist->nbins, b.res, np, hist->host, s));
     }
     if (ev) {
         const heget::GenParams gp = slice_gen_params(n, *cfg);
@@ -817,14 +820,10 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
             HG_HIP(hipMemcpyAsync(ev->momenta_soa, b.mom, sizeof(double) * size_t(n + 2) * 4 * size_t(np),
                                   hipMemcpyDeviceToHost, s));
     }
-    if (!d_out) {
-        const unsigned slot = g.ring.fetch_add(1) % kRing;
-        double *staged = g.pinned + 8 * slot;
-        HG_HIP(hipMemcpyAsync(staged, b.res, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
+    if (out) {
         XsecTicket *t = new XsecTicket{out, staged, np};
         HG_HIP(hipLaunchHostFunc(s, xsec_finish, t));
     }
-    if (flags_out) *flags_out = flags;
     return HEGET_OK;
 }
 
@@ -900,13 +899,10 @@ heget_status batch_enqueue_branches(int ncfg, const int *n, const heget_config *
         HG_HIP(hipStreamWaitEvent(si, g.fork, 0));
         HG_TRY(enqueue_generation(n[i], c, b, si));
         HG_HIP(heget::launch_me2(*pick_variant(c.prec, n[i]), mc_me2_args(n[i], c, b, flags), si));
-        HG_TRY(enqueue_reduction(c, b, flags, nullptr, si));
-        HG_HIP(hipMemcpyAsync(staged + 4 * i, b.res, 4 * sizeof(double), hipMemcpyDeviceToHost, si));
+        HG_TRY(enqueue_reduction(c, b, flags, nullptr, staged + kStaged * i, si));
         HG_HIP(hipEventRecord(g.join[i], si));
         HG_HIP(hipStreamWaitEvent(s, g.join[i], 0));
     }
-    HG_HIP(hipMemcpyAsync(staged + 4 * heget::kMaxSlices, flags, sizeof(unsigned),
-                          hipMemcpyDeviceToHost, s));
     return HEGET_OK;
 }
 
@@ -944,12 +940,8 @@ heget_status batch_enqueue(int ncfg, const int *n, const heget_config *cfgs, Sli
     const int grid = cus * heget::me2_batch_blocks_per_cu(cfgs[0].prec);
     HG_HIP(heget::launch_me2_batch(cfgs[0].prec, bd, grid, s));
     for (int i = 0; i < ncfg; ++i) {
-        HG_TRY(enqueue_reduction(cfgs[i], sb[i].b, flags, nullptr, s));
-        HG_HIP(hipMemcpyAsync(staged + 4 * i, sb[i].b.res, 4 * sizeof(double),
-                              hipMemcpyDeviceToHost, s));
+        HG_TRY(enqueue_reduction(cfgs[i], sb[i].b, flags, nullptr, staged + kStaged * i, s));
     }
-    HG_HIP(hipMemcpyAsync(staged + 4 * heget::kMaxSlices, flags, sizeof(unsigned),
-                          hipMemcpyDeviceToHost, s));
     return HEGET_OK;
 }
 
@@ -973,6 +965,14 @@ heget_result make_result(const double *st, int64_t n_gen)
     const double var = n_gen > 1 ? (sum2 / double(n_gen) - r.sigma_fb * r.sigma_fb) / double(n_gen - 1) : 0.0;
     r.err_fb = std::sqrt(var > 0.0 ? var : 0.0);
     return r;
+}
+
+// Wait for a call enqueued on the library stream and read its pinned result.
+heget_status xsec_wait(const double *staged, int64_t np, heget_result *out)
+{
+    HG_HIP(hipStreamSynchronize(g.stream));
+    *out = make_result(staged, np);
+    return mc_flags_status(static_cast<unsigned>(staged[4]));
 }
 
 // Bytes of the S_BATCH slot that the batch needs under one schedule.
@@ -1382,7 +1382,7 @@ heget_status heget_xsec_device_noalloc(int n, const heget_config *cfg, heget_res
     hipStream_t s = static_cast<hipStream_t>(stream);
     HG_TRY(enqueue_generation(n, *cfg, b, s, flags));  // also clears flags
     HG_HIP(heget::launch_me2(*v, mc_me2_args(n, *cfg, b, flags), s));
-    HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, s));
+    HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, nullptr, s));
     return HEGET_OK;
 }
 
@@ -1397,12 +1397,9 @@ heget_status heget_xsec(int n, const heget_config *cfg, heget_result *out)
     }
     std::lock_guard<std::mutex> lk(g_mu);
     HG_TRY(ensure_device());
-    unsigned *d_flags = nullptr;
-    HG_TRY(xsec_enqueue(n, cfg, out, nullptr, g.stream, &d_flags));
-    unsigned flags = 0;
-    HG_HIP(hipMemcpyAsync(&flags, d_flags, sizeof(unsigned), hipMemcpyDeviceToHost, g.stream));
-    HG_HIP(hipStreamSynchronize(g.stream));
-    return mc_flags_status(flags);
+    double *staged = nullptr;
+    HG_TRY(xsec_enqueue(n, cfg, nullptr, nullptr, g.stream, &staged));
+    return xsec_wait(staged, cfg->npoints, out);
 }
 
 heget_status heget_xsec_hist(int n, const heget_config *cfg, int observable, int nbins, double lo,
@@ -1424,13 +1421,15 @@ heget_status heget_xsec_hist(int n, const heget_config *cfg, int observable, int
     }
     std::lock_guard<std::mutex> lk(g_mu);
     HG_TRY(ensure_device());
-    unsigned *d_flags = nullptr;
-    const HistReq req{observable, nbins, lo, hi, hist};
-    HG_TRY(xsec_enqueue(n, cfg, out, nullptr, g.stream, &d_flags, &req));
-    unsigned flags = 0;
-    HG_HIP(hipMemcpyAsync(&flags, d_flags, sizeof(unsigned), hipMemcpyDeviceToHost, g.stream));
-    HG_HIP(hipStreamSynchronize(g.stream));
-    return mc_flags_status(flags);
+    if (!g.pinned_hist)
+        HG_HIP(hipHostMalloc(reinterpret_cast<void **>(&g.pinned_hist),
+                             sizeof(double) * (heget::kHistMaxBins + 2), hipHostMallocDefault));
+    double *staged = nullptr;
+    const HistReq req{observable, nbins, lo, hi, g.pinned_hist};
+    HG_TRY(xsec_enqueue(n, cfg, nullptr, nullptr, g.stream, &staged, &req));
+    const heget_status st = xsec_wait(staged, cfg->npoints, out);
+    if (st >= 0) std::memcpy(hist, g.pinned_hist, sizeof(double) * size_t(nbins + 2));
+    return st;
 }
 
 heget_status heget_xsec_events(int n, const heget_config *cfg, heget_result *out, double *weight,
@@ -1450,18 +1449,16 @@ heget_status heget_xsec_events(int n, const heget_config *cfg, heget_result *out
     if (momenta) HG_TRY(host_buffer(soa, size_t(n + 2) * 4 * size_t(np)));
     std::lock_guard<std::mutex> lk(g_mu);
     HG_TRY(ensure_device());
-    unsigned *d_flags = nullptr;
+    double *staged = nullptr;
     const EventReq req{weight, momenta ? soa.data() : nullptr, rapidity, helicity};
-    HG_TRY(xsec_enqueue(n, cfg, out, nullptr, g.stream, &d_flags, nullptr, &req));
-    unsigned flags = 0;
-    HG_HIP(hipMemcpyAsync(&flags, d_flags, sizeof(unsigned), hipMemcpyDeviceToHost, g.stream));
-    HG_HIP(hipStreamSynchronize(g.stream));
-    if (momenta) {
+    HG_TRY(xsec_enqueue(n, cfg, nullptr, nullptr, g.stream, &staged, nullptr, &req));
+    const heget_status st = xsec_wait(staged, np, out);
+    if (st >= 0 && momenta) {
         const size_t rows = size_t(n + 2) * 4;
         for (int64_t i = 0; i < np; ++i)
             for (size_t r = 0; r < rows; ++r) momenta[size_t(i) * rows + r] = soa[r * size_t(np) + size_t(i)];
     }
-    return mc_flags_status(flags);
+    return st;
 }
 
 heget_status heget_set_batch_schedule(int schedule)
@@ -1508,7 +1505,7 @@ heget_status heget_xsec_batch(const int *n, const heget_config *cfgs, int ncfg,
         BatchGraph nb;
         nb.key = key;
         HG_HIP(hipHostMalloc(reinterpret_cast<void **>(&nb.staged),
-                             sizeof(double) * 4 * (heget::kMaxSlices + 1), hipHostMallocDefault));
+                             sizeof(double) * kStaged * heget::kMaxSlices, hipHostMallocDefault));
         // One S_BATCH slot of the size the largest schedule needs, obtained
         // before any capture: growing the slot frees the old memory, which a
         // graph captured earlier in this call would still address.
@@ -1548,9 +1545,12 @@ heget_status heget_xsec_batch(const int *n, const heget_config *cfgs, int ncfg,
     }
     HG_HIP(hipGraphLaunch(bg->exec, s));
     HG_HIP(hipStreamSynchronize(s));
-    for (int i = 0; i < ncfg; ++i) out[i] = make_result(bg->staged + 4 * i, cfgs[i].npoints);
-    unsigned fl = 0;
-    std::memcpy(&fl, bg->staged + 4 * heget::kMaxSlices, sizeof(unsigned));
+    unsigned fl = 0;  // one flag word for the batch: a slice reports what was set when it ended
+    for (int i = 0; i < ncfg; ++i) {
+        const double *st = bg->staged + kStaged * i;
+        out[i] = make_result(st, cfgs[i].npoints);
+        fl |= static_cast<unsigned>(st[4]);
+    }
     return mc_flags_status(fl);
 }
 
@@ -1797,6 +1797,8 @@ void heget_shutdown(void)
     g.fork = nullptr;
     if (g.pinned) (void)hipHostFree(g.pinned);
     g.pinned = nullptr;
+    if (g.pinned_hist) (void)hipHostFree(g.pinned_hist);
+    g.pinned_hist = nullptr;
     if (g.stream) (void)hipStreamDestroy(g.stream);
     g.stream = nullptr;
     g.ready = false;

@@ -136,9 +136,10 @@ hipError_t launch_hist_finish(const unsigned long long *bins, int nbins, const d
                               int64_t n_gen, double *hist, hipStream_t stream);
 // Fixed-order compensated reduction of the ceil(*d_count / 64) tile triples
 // into res[0..3] = (sum + compensation, compensation, sum of squares, *d_count)
-// and, if `record` is set, the heget_result record for n_gen generated points.
+// and, if `record` is set, the heget_result record for n_gen generated points;
+// if `host` is set (pinned host memory), res[0..3] and *flags into host[0..4].
 hipError_t launch_final(const double *partials, const int64_t *d_count, int64_t n_gen, double *res,
-                        void *record, hipStream_t stream);
+                        void *record, const unsigned *flags, double *host, hipStream_t stream);
 // FMA issue-rate probe: blocks x 256 threads, iters x 128 FMAs per thread into
 // out[blocks * 256] (float for prec 1, double for prec 0); its flop count.
 hipError_t launch_fma_peak(int prec, void *out, int blocks, int iters, hipStream_t stream);

@@ -291,10 +291,12 @@ __device__ __forceinline__ void block_reduce(CSum &cs, double &sq)
 // One block: thread t folds tiles t, t + T, t + 2T, ... in that order (loads
 // issued kFinalBatch at a time), then a fixed tree.  The record is {sigma,
 // err, sum, comp, sum2 (double), n_gen, n_acc (int64)}, sigma = sum / n_gen
-// and err^2 = (sum2/N - sigma^2)/(N - 1).
+// and err^2 = (sum2/N - sigma^2)/(N - 1).  `host` (pinned host memory) receives
+// res and the call's status flags: the host needs no copy after the kernel.
 __global__ void __launch_bounds__(kFinalThreads)
 final_kernel(const double *__restrict__ partials, const int64_t *__restrict__ d_count,
-             int64_t n_gen, double *__restrict__ res, void *record)
+             int64_t n_gen, double *__restrict__ res, void *record,
+             const unsigned *__restrict__ flags, double *__restrict__ host)
 {
     const int64_t nacc = *d_count;
     const int64_t nt = (nacc + 63) / 64;
@@ -324,6 +326,13 @@ final_kernel(const double *__restrict__ partials, const int64_t *__restrict__ d_
     res[1] = cs.c;
     res[2] = sq;
     res[3] = static_cast<double>(nacc);
+    if (host) {
+        host[0] = sum;
+        host[1] = cs.c;
+        host[2] = sq;
+        host[3] = static_cast<double>(nacc);
+        host[4] = static_cast<double>(*flags);
+    }
     if (record) {
         double *d = static_cast<double *>(record);
         int64_t *q = static_cast<int64_t *>(record);
@@ -518,10 +527,10 @@ hipError_t launch_sum_chunks(const double *part, int nchunks, int64_t ld, const 
 }
 
 hipError_t launch_final(const double *partials, const int64_t *d_count, int64_t n_gen, double *res,
-                        void *record, hipStream_t stream)
+                        void *record, const unsigned *flags, double *host, hipStream_t stream)
 {
     hipLaunchKernelGGL(final_kernel, dim3(1), dim3(kFinalThreads), 0, stream, partials, d_count,
-                       n_gen, res, record);
+                       n_gen, res, record, flags, host);
     return hipGetLastError();
 }
 
