@@ -283,15 +283,28 @@ double me2_coef(int n, double alpha, double charge)
 
 double me2_flops_per_point(int n, int mb, int h, int cl, int ps = 0);
 
-// Helicity chunks per work item: enough wave-sized items for small batches
-// (>= 8192), and no item above ~2e8 flops so the tail of a launch stays short.
+// Helicity chunks per work item.  A walk is split while its items, doubled,
+// still find a SIMD each (kFillItems: one wave for each of 4 SIMDs on 256 CUs)
+// and an item's work is worth the pass that sums the chunks, and where one item
+// alone would be a long tail.  Lines from sweeps of heget_me2_device over 64 ..
+// 1e6 points, n = 2 .. 5: splitting further repeats the set-up and the momentum
+// part and adds rounds (n = 5 FP32, 130 000 points: 59 us whole, 95 us in 8192
+// items; n = 4 FP64: 50 000 points 11.4 us whole, 17 in two, 520 000 points 78
+// against 99 us in 8192 items); an item of fewer operations than kSplitFlops
+// takes less than that pass (n = 3 FP64, 1.5e5: 7.7 us whole, 10.4 in two), one
+// of more takes longer (n = 5 FP32, 1.7e6: 500 points 19 us whole, 14 in four).
+constexpr int64_t kFillItems = 1024;
+constexpr double kSplitFlops = 2e5;
+constexpr double kTailFlops = 2e8;
+
 int plan_chunks_shape(int n, int mb, int h, int cl, int ps, int64_t points_expected)
 {
     const int passes = (1 << n) / h;
     const int64_t tiles = (points_expected + 63) / 64;
     const double item_flops = 64.0 * me2_flops_per_point(n, mb, h, cl, ps);
     int c = 1;
-    while (c < passes && (tiles * c < 8192 || item_flops / c > 2e8)) c *= 2;
+    while (c < passes && ((tiles * 2 * c <= kFillItems && item_flops / c > kSplitFlops) || item_flops / c > kTailFlops))
+        c *= 2;
     return c;
 }
 
