@@ -319,8 +319,8 @@ const heget::Me2Variant *g_tuned[2][9] = {};
 // The kernel without a chosen shape: helicities over the lanes of a wave where
 // it is compiled (n >= 6), else the first walk shape.  From n = 6 a lane holds
 // too few helicities to share the currents (points/s, walk against lanes, at
-// 1, 517 and about 1e5 points alike: n = 6 FP32 3.3e8 against 6.2e8, FP64
-// 9.7e7 against 3.6e8; n = 8 1.2e6 against 3.8e7 in FP64); at n = 5 the walk
+// 1, 517 and about 1e5 points alike: n = 6 FP32 3.3e8 against 7.6e8, FP64
+// 9.7e7 against 4.8e8; n = 8 1.2e6 against 5.1e7 in FP64); at n = 5 the walk
 // holds eight of 32 in registers and wins (FP32 1.24e9 against 1.07e9, FP64
 // 6.1e8 against 5.6e8 at 200 003 points).
 const heget::Me2Variant *default_variant(int prec, int n)

@@ -91,13 +91,13 @@ hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream)
 {
     const int64_t ntiles = (a.count + 63) / 64;
     int64_t items = (ntiles + v.ppl - 1) / v.ppl * a.nchunks;
-    if (v.ps == kLanesPs) {  // 2^(8 - n) points per wave, |M|^2 of each to out
+    if (v.ps == kLanesPs) {  // a workgroup's wave(s) share 2^(8 - n) points, |M|^2 of each to out
         const int64_t per = int64_t(1) << (8 - v.n);
         if (a.nchunks != 1 || a.partials || !a.out) return hipErrorInvalidValue;
         items = (a.count + per - 1) / per;
     }
     if (items == 0) return hipSuccess;
-    int64_t blocks = (items + v.wpb - 1) / v.wpb;
+    int64_t blocks = v.ps == kLanesPs ? items : (items + v.wpb - 1) / v.wpb;
     if (v.pf) {
         const int64_t r = resident_blocks(v);
         if (r > 0 && r < blocks) blocks = r;
