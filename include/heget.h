@@ -331,11 +331,13 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
 heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape *chosen,
                             double *ms);
 
-/* The compiled walk shapes (prefix_sets <= 4) for (n, prec), the one in use
- * first, into shapes[i] for i < max (shapes may be NULL when max = 0); *count
- * receives how many exist.  The kernel of prefix_sets = 5 is not among them:
- * heget_me2_flops names it where it is in use, and heget_set_kernel_shape
- * takes its shape. */
+/* The compiled walk shapes for (n, prec), the one in use first, into shapes[i]
+ * for i < max (shapes may be NULL when max = 0); *count receives how many
+ * exist.  The kernels that form every subset current once per point
+ * (helicities_per_walk = 2^n; the defaults for n >= 6 and for n = 5 FP32) are
+ * not among them: heget_me2_flops names them where they are in use, and
+ * heget_set_kernel_shape takes their shapes.  Without a chosen shape n = 5
+ * calls of up to 32768 points run a walk of fewer helicities. */
 heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *shapes, int *count);
 
 /* Use a compiled shape for (n, prec) from now on in this process; NULL

@@ -316,23 +316,36 @@ int plan_chunks(const heget::Me2Variant &v, int64_t points_expected)
 // Shape chosen by the autotuner (or loaded from the tuning cache) per (prec, n).
 const heget::Me2Variant *g_tuned[2][9] = {};
 
-// The kernel without a chosen shape: helicities over the lanes of a wave where
-// it is compiled (n >= 6), else the first walk shape.  From n = 6 a lane holds
-// too few helicities to share the currents (points/s, walk against lanes, at
-// 1, 517 and about 1e5 points alike: n = 6 FP32 3.3e8 against 7.6e8, FP64
-// 9.7e7 against 4.8e8; n = 8 1.2e6 against 5.1e7 in FP64); at n = 5 the walk
-// holds eight of 32 in registers and wins (FP32 1.24e9 against 1.07e9, FP64
-// 6.1e8 against 5.6e8 at 200 003 points).
-const heget::Me2Variant *default_variant(int prec, int n)
+const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, int wpb, int pf, int wpe,
+                                      int ppl, int ps);
+
+// The kernel without a chosen shape for calls of about `points` points.
+// n >= 6: helicities over the lanes of a wave.  From n = 6 a lane holds too few
+// helicities to share the currents (points/s, walk against lanes, at 1, 517
+// and about 1e5 points alike: n = 6 FP32 3.3e8 against 7.6e8, FP64 9.7e7
+// against 4.8e8; n = 8 1.2e6 against 5.1e7 in FP64).
+// n = 5: a walk of all 32 configurations (FP32) or eight (FP64, the first
+// shape of the list); lanes would run at 1.07e9 and 5.6e8 points/s against
+// 2.7e9 and 1.1e9.  Below one wave per two SIMDs (kFillItems / 2 tiles) a walk
+// of fewer configurations that splits into chunks ends sooner: 500 points 14
+// instead of 23 us (FP32, eight), 14 instead of 18 us (FP64, four); at 20 000
+// points 19 against 25 us (FP32) and 36 against 37 us (FP64).
+// n <= 4: the first shape of the list.
+const heget::Me2Variant *default_variant(int prec, int n, int64_t points)
 {
-    const heget::Me2Variant *l = heget::me2_lanes(prec, n);
-    return l ? l : heget::me2_default(prec, n);
+    if (n == 5 && (points + 63) / 64 <= kFillItems / 2) {
+        const heget::Me2Variant *few = prec == HEGET_FP32 ? find_variant(prec, 5, 5, 8, 2, 1, 0, 0, 1, 2)
+                                                          : find_variant(prec, 5, 5, 4, 2, 1, 0, 0, 1, 3);
+        if (few) return few;
+    }
+    const heget::Me2Variant *all = heget::me2_shared(prec, n);
+    return all ? all : heget::me2_default(prec, n);
 }
 
-const heget::Me2Variant *pick_variant(int prec, int n)
+const heget::Me2Variant *pick_variant(int prec, int n, int64_t points)
 {
     if (prec >= 0 && prec < 2 && n >= 2 && n <= 8 && g_tuned[prec][n]) return g_tuned[prec][n];
-    return default_variant(prec, n);
+    return default_variant(prec, n, points);
 }
 
 // The amplitude kernel writes |M|^2 per point and the weighted sums follow in
@@ -350,8 +363,8 @@ const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, in
     const heget::Me2Variant *v = heget::me2_variants(&cnt);
     for (int i = 0; i < cnt; ++i)
         if (is(v[i])) return &v[i];
-    const heget::Me2Variant *l = heget::me2_lanes(prec, n);
-    return l && is(*l) ? l : nullptr;
+    const heget::Me2Variant *all = heget::me2_shared(prec, n);
+    return all && is(*all) ? all : nullptr;
 }
 
 heget_shape shape_of(const heget::Me2Variant &v)
@@ -606,7 +619,7 @@ heget_status collect_timing()
 heget_status me2_on_device(int n, int64_t np, const double *d_mom, double *d_out, int prec,
                            hipStream_t s, unsigned *d_flags)
 {
-    const heget::Me2Variant *v = pick_variant(prec, n);
+    const heget::Me2Variant *v = pick_variant(prec, n, np);
     if (!v) return fail(HEGET_ERR_ARG, "no compiled amplitude kernel for this n/precision");
     const int nchunks = plan_chunks(*v, np);
     double *part = d_out;
@@ -772,7 +785,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     const int64_t np = cfg->npoints;
     const bool sampled = cfg->helicity_sampling != 0;
     const heget::Me2Variant *v =
-        sampled ? heget::me2_sampled(cfg->prec, n) : pick_variant(cfg->prec, n);
+        sampled ? heget::me2_sampled(cfg->prec, n) : pick_variant(cfg->prec, n, np / 2);
     if (!v) return fail(HEGET_ERR_ARG, "no compiled amplitude kernel for this n/precision");
 
     const int64_t nb = (np + 255) / 256;
@@ -874,7 +887,7 @@ void carve_batch(Arena &ar, int ncfg, const int *n, const heget_config *cfgs, in
         if (schedule == 1) {
             heget::me2_batch_shape(cfgs[s].prec, n[s], &sl.mb, &sl.h, &sl.cl, &sl.ps);
         } else {
-            const heget::Me2Variant *v = pick_variant(cfgs[s].prec, n[s]);
+            const heget::Me2Variant *v = pick_variant(cfgs[s].prec, n[s], np / 2);
             sl.mb = v->mb;
             sl.h = v->h;
             sl.cl = v->cl;
@@ -891,7 +904,7 @@ void carve_batch(Arena &ar, int ncfg, const int *n, const heget_config *cfgs, in
         b.wout = nullptr;
         b.d_count = ar.take<int64_t>(1);
         // the persistent kernel always writes |M|^2 per chunk
-        b.apart = schedule == 1 || sums_apart(*pick_variant(cfgs[s].prec, n[s]), b.nchunks);
+        b.apart = schedule == 1 || sums_apart(*pick_variant(cfgs[s].prec, n[s], np / 2), b.nchunks);
         b.part = b.apart ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
         b.partials = ar.take<double>(size_t(3) * size_t((np + 63) / 64 + 1));  // + spare tile slot
         b.res = ar.take<double>(4);
@@ -911,7 +924,7 @@ heget_status batch_enqueue_branches(int ncfg, const int *n, const heget_config *
         const McBufs &b = sb[i].b;
         HG_HIP(hipStreamWaitEvent(si, g.fork, 0));
         HG_TRY(enqueue_generation(n[i], c, b, si));
-        HG_HIP(heget::launch_me2(*pick_variant(c.prec, n[i]), mc_me2_args(n[i], c, b, flags), si));
+        HG_HIP(heget::launch_me2(*pick_variant(c.prec, n[i], c.npoints / 2), mc_me2_args(n[i], c, b, flags), si));
         HG_TRY(enqueue_reduction(c, b, flags, nullptr, staged + kStaged * i, si));
         HG_HIP(hipEventRecord(g.join[i], si));
         HG_HIP(hipStreamWaitEvent(s, g.join[i], 0));
@@ -1375,7 +1388,7 @@ heget_status heget_xsec_device_noalloc(int n, const heget_config *cfg, heget_res
     const bool sampled = cfg->helicity_sampling != 0;
     std::lock_guard<std::mutex> lk(g_mu);
     const heget::Me2Variant *v =
-        sampled ? heget::me2_sampled(cfg->prec, n) : pick_variant(cfg->prec, n);
+        sampled ? heget::me2_sampled(cfg->prec, n) : pick_variant(cfg->prec, n, cfg->npoints / 2);
     if (!v) return fail(HEGET_ERR_ARG, "no compiled amplitude kernel for this n/precision");
     McBufs b;
     unsigned *flags = nullptr;
@@ -1617,11 +1630,11 @@ heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape
     HG_HIP(hipEventCreate(&e1));
     int cnt = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
-    const heget::Me2Variant *lanes = heget::me2_lanes(prec, n);
+    const heget::Me2Variant *shared = heget::me2_shared(prec, n);
     const heget::Me2Variant *best = nullptr;
     double best_ms = 0.0;
-    for (int i = lanes ? -1 : 0; i < cnt; ++i) {
-        const heget::Me2Variant &v = i < 0 ? *lanes : all[i];
+    for (int i = shared ? -1 : 0; i < cnt; ++i) {
+        const heget::Me2Variant &v = i < 0 ? *shared : all[i];
         if (v.prec != prec || v.n != n) continue;
         const int nchunks = plan_chunks(v, npoints);
         double *out = nullptr;
@@ -1682,8 +1695,8 @@ heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *s
     if (!count || (max > 0 && !shapes)) return fail(HEGET_ERR_ARG, "null pointer");
     int cnt = 0, k = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
-    const heget::Me2Variant *cur = pick_variant(prec, n);
-    if (cur && cur->ps == heget::kLanesPs) cur = heget::me2_default(prec, n);  // no walk shape
+    const heget::Me2Variant *cur = pick_variant(prec, n, kMaxPoints);
+    if (cur == heget::me2_shared(prec, n)) cur = heget::me2_default(prec, n);  // not in the list
     if (cur) {  // the shape in use first
         if (k < max) shapes[k] = shape_of(*cur);
         ++k;
@@ -1737,7 +1750,7 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
     HG_TRY(check_n(n));
     HG_TRY(check_prec(prec));
     if (!flops_per_point) return fail(HEGET_ERR_ARG, "null pointer");
-    const heget::Me2Variant *v = pick_variant(prec, n);
+    const heget::Me2Variant *v = pick_variant(prec, n, kMaxPoints);
     if (!v) return fail(HEGET_ERR_ARG, "no compiled amplitude kernel for this n/precision");
     *flops_per_point = me2_flops_per_point(n, v->mb, v->h, v->cl, v->ps);
     if (shape) *shape = shape_of(*v);

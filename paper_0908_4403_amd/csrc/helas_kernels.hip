@@ -127,7 +127,7 @@ __device__ inline Cx<double> product(const Spinor &p, const Spinor &q)
 // latency.  Time, with the chains over all orderings of 4-spinors for both
 // quark helicities that this replaces -> now: 20 011 points n = 4 FP64 563 ->
 // 13.5 us, n = 5 FP64 5570 -> 48 us, n = 5 FP32 5150 -> 27 us; 200 003 points
-// n = 3 FP64 161 -> 17 us, n = 4 FP32 1040 -> 33 us, n = 5 FP64 22.5 -> 0.30
+// n = 3 FP64 161 -> 17 us, n = 4 FP32 1040 -> 33 us, n = 5 FP64 22.5 -> 0.23
 // ms; n = 2 is bound by the launch on both.  Errors against 64-bit values are
 // no larger (median at n = 4 2.2e-15 -> 2.0e-15 in FP64, 7.9e-7 -> 1.1e-7 in
 // FP32; at a boost of gamma = 20 1.5e-12 -> 9e-15 and 8e-4 -> 1.1e-7).
@@ -208,7 +208,9 @@ hipError_t launch_frame_n(int64_t np, const double *mom, int64_t ld, double coef
 }
 
 // The walk shapes (helicities per walk, closing, prefix sets; helicities per
-// walk where four waves share a point) follow the amplitude kernel's defaults.
+// walk where four waves share a point) follow the amplitude kernel's defaults,
+// but for n = 5 FP32, where all 32 helicities per walk spill here (200 003
+// points 154 us, eight per walk 132).
 template <typename R>
 hipError_t launch_frame(int n, int64_t np, const double *mom, int64_t ld, double coef, double *out,
                         unsigned *flags, hipStream_t s)
@@ -217,8 +219,8 @@ hipError_t launch_frame(int n, int64_t np, const double *mom, int64_t ld, double
     switch (n) {
     case 2: return launch_frame_n<R, 2, 2, 2, 0, 2>(np, mom, ld, coef, out, flags, s);
     case 3: return launch_frame_n<R, 3, f32 ? 8 : 4, 2, 0, 4>(np, mom, ld, coef, out, flags, s);
-    case 4: return launch_frame_n<R, 4, f32 ? 16 : 4, 3, 0, 4>(np, mom, ld, coef, out, flags, s);
-    case 5: return launch_frame_n<R, 5, f32 ? 8 : 2, 2, 2, f32 ? 8 : 2>(np, mom, ld, coef, out, flags, s);
+    case 4: return launch_frame_n<R, 4, 16, 3, 0, 4>(np, mom, ld, coef, out, flags, s);
+    case 5: return launch_frame_n<R, 5, 8, 2, f32 ? 2 : 3, f32 ? 8 : 4>(np, mom, ld, coef, out, flags, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -34,8 +34,10 @@ constexpr int kLanesPs = 5;
 // All compiled walk variants (one lane per point; static table) and the first one per (prec, n).
 const Me2Variant *me2_variants(int *count);
 const Me2Variant *me2_default(int prec, int n);
-// The kernel with a point's helicities over the lanes of a wave for (prec, n), or nullptr.
-const Me2Variant *me2_lanes(int prec, int n);
+// The kernel that forms every subset current once per point for (prec, n), outside the list of
+// walk variants, or nullptr: helicities over the lanes of a wave (me2_lanes.hpp) or, for the
+// float n = 5, one walk of all of them.
+const Me2Variant *me2_shared(int prec, int n);
 // The helicity-sampling kernel (h = 0) for (prec, n).
 const Me2Variant *me2_sampled(int prec, int n);
 

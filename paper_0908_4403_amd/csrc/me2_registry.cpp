@@ -20,6 +20,8 @@ extern const Me2Variant kShapesSampled[], kShapesSampledMeet8[];
 extern const int kShapesSampledCount, kShapesSampledMeet8Count;
 extern const Me2Variant kShapesLanes[];
 extern const int kShapesLanesCount;
+extern const Me2Variant kShapesWhole[];
+extern const int kShapesWholeCount;
 
 static const std::vector<Me2Variant> &all_variants()
 {
@@ -52,10 +54,12 @@ const Me2Variant *me2_default(int prec, int n)
     return nullptr;
 }
 
-const Me2Variant *me2_lanes(int prec, int n)
+const Me2Variant *me2_shared(int prec, int n)
 {
     for (int i = 0; i < kShapesLanesCount; ++i)
         if (kShapesLanes[i].prec == prec && kShapesLanes[i].n == n) return &kShapesLanes[i];
+    for (int i = 0; i < kShapesWholeCount; ++i)
+        if (kShapesWhole[i].prec == prec && kShapesWhole[i].n == n) return &kShapesWhole[i];
     return nullptr;
 }
 
