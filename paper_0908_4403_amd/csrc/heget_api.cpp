@@ -719,14 +719,17 @@ heget::GenParams slice_gen_params(int n, const heget_config &c)
 }
 
 // Generation and compaction: every point's momenta and weight factor, the
-// survivor list (point order) and the survivor count in *d_count; `clear`
-// (optional) is zeroed by the generation launch.
+// survivor list (point order) and the survivor count in *d_count; `clear` and
+// `bins` (optional) are zeroed by the generation launch.
 heget_status enqueue_generation(int n, const heget_config &c, const McBufs &b, hipStream_t s,
-                                unsigned *clear = nullptr)
+                                unsigned *clear = nullptr, unsigned long long *bins = nullptr,
+                                int bin_words = 0)
 {
     const int64_t np = c.npoints;
     heget::GenParams gp = slice_gen_params(n, c);
     gp.clear_word = clear;
+    gp.bins = bins;
+    gp.bin_words = bin_words;
     gp.hel_out = b.hel;
     HG_HIP(heget::launch_gen(n, gp, b.mom, np, b.wfac, b.flag, b.bcount, s));
     HG_HIP(heget::launch_compact(b.bcount, b.flag, np, b.index, b.d_count, s));
@@ -743,16 +746,22 @@ heget_status enqueue_reduction(const heget_config &c, const McBufs &b, unsigned 
     if (b.apart)
         HG_HIP(heget::launch_sum_chunks(b.part, b.nchunks, np, b.d_count, np, nullptr, b.index,
                                         b.wfac, b.partials, b.wout, flags, s));
-    HG_HIP(heget::launch_final(b.partials, b.d_count, np, b.res, record, flags, staged, s));
+    HG_HIP(heget::launch_final(b.partials, b.d_count, nullptr, np, b.res, record, flags, staged, s));
     return HEGET_OK;
 }
 
-// Arguments of the amplitude pass of a Monte-Carlo call.  With helicity
-// sampling the per-point value is the estimator 2^(n+1) |M_h|^2 of the drawn
-// configuration: 2^n times the kernel's two-block coefficient.
+// Coefficient of |M|^2 in a Monte-Carlo call.  With helicity sampling the
+// per-point value is the estimator 2^(n+1) |M_h|^2 of the drawn configuration:
+// 2^n times the kernel's two-block coefficient.
+double mc_coef(int n, const heget_config &c)
+{
+    return me2_coef(n, c.alpha, c.charge) * (c.helicity_sampling ? double(1 << n) : 1.0);
+}
+
+// Arguments of the amplitude pass of a Monte-Carlo call.
 heget::Me2Args mc_me2_args(int n, const heget_config &c, const McBufs &b, unsigned *flags)
 {
-    const double coef = me2_coef(n, c.alpha, c.charge) * (b.hel ? double(1 << n) : 1.0);
+    const double coef = mc_coef(n, c);
     const bool epi = !b.apart;
     return heget::Me2Args{b.mom,      c.npoints,  b.index,  b.hel,  b.d_count,
                           c.npoints,  b.nchunks,  coef,     b.part, c.npoints,
@@ -765,6 +774,30 @@ struct HistReq {
     double lo, hi;
     double *host;  // [nbins + 2], pinned, written by the last kernel
 };
+
+// Whether a cross section runs as one fused kernel (the reasons stand in mc_fused.hip): not with a chosen kernel shape, or when
+// the amplitude kernel is to be timed.
+bool runs_fused(int n, const heget_config &c)
+{
+    const bool sampled = c.helicity_sampling != 0;
+    return heget::has_fused(n, c.prec, sampled, c.npoints) && !g.timing && (sampled || !g_tuned[c.prec][n]);
+}
+
+// The fused path into b.res, the result record and the pinned result; each
+// generated point's weight into w (optional) and, with hist, its observable
+// into x.
+heget_status enqueue_fused(int n, const heget_config &c, const McBufs &b, void *record, double *staged,
+                           hipStream_t s, double *w = nullptr, const HistReq *hist = nullptr,
+                           double *x = nullptr, unsigned long long *bins = nullptr)
+{
+    heget::GenParams gp = slice_gen_params(n, c);
+    gp.bins = bins;
+    gp.bin_words = hist ? hist->nbins + 3 : 0;
+    HG_HIP(heget::launch_fused(n, c.prec, c.helicity_sampling != 0, gp, mc_coef(n, c), b.partials, b.bcount,
+                               w, hist ? x : nullptr, hist ? hist->observable : 0, s));
+    HG_HIP(heget::launch_final(b.partials, nullptr, b.bcount, c.npoints, b.res, record, nullptr, staged, s));
+    return HEGET_OK;
+}
 
 // Per-event records to copy out beside the cross section (heget_xsec_events):
 // host arrays of npoints entries (momenta_soa: (n + 2) * 4 rows of npoints).
@@ -792,16 +825,21 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     McBufs b{};
     b.nchunks = sampled ? 1 : plan_chunks(*v, np / 2);
     b.apart = sums_apart(*v, b.nchunks);
+    const bool fused = runs_fused(n, *cfg);
+    const size_t keep = fused ? 0 : size_t(np);  // points whose data goes through memory
     unsigned *flags;
     HG_TRY(scratch_bind(s));
-    HG_TRY(scratch_t<double>(S_MOM, size_t(n + 2) * 4 * size_t(np), &b.mom));
-    HG_TRY(scratch_t<double>(S_WFAC, size_t(np), &b.wfac));
-    HG_TRY(scratch_t<uint8_t>(S_FLAG, size_t(np), &b.flag));
+    // a fused histogram keeps each point's observable in place of its momenta
+    const bool events_mom = ev && ev->momenta_soa;
+    HG_TRY(scratch_t<double>(S_MOM, fused && hist ? size_t(np) : size_t(n + 2) * 4 * (events_mom ? size_t(np) : keep),
+                             &b.mom));
+    HG_TRY(scratch_t<double>(S_WFAC, events_mom ? size_t(np) : keep, &b.wfac));
+    HG_TRY(scratch_t<uint8_t>(S_FLAG, keep, &b.flag));
     HG_TRY(scratch_t<int32_t>(S_BCOUNT, size_t(nb), &b.bcount));
     HG_TRY(scratch_t<int64_t>(S_COUNT, 1, &b.d_count));
-    HG_TRY(scratch_t<int32_t>(S_INDEX, size_t(np), &b.index));
+    HG_TRY(scratch_t<int32_t>(S_INDEX, keep, &b.index));
     b.hel = nullptr;
-    if (sampled) HG_TRY(scratch_t<uint16_t>(S_HEL, size_t(np), &b.hel));
+    if (sampled) HG_TRY(scratch_t<uint16_t>(S_HEL, keep, &b.hel));
     b.wout = nullptr;
     unsigned long long *bins = nullptr;
     if (hist || ev) HG_TRY(scratch_t<double>(S_WOUT, size_t(np), &b.wout));
@@ -812,29 +850,37 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
         if (ev->rapidity) HG_TRY(scratch_t<double>(S_EVY, size_t(np), &ev_y));
         if (ev->helicity) HG_TRY(scratch_t<uint16_t>(S_EVH, size_t(np), &ev_h));
     }
-    if (hist) HG_TRY(scratch_t<unsigned long long>(S_BINS, size_t(hist->nbins) + 2, &bins));
+    if (hist) HG_TRY(scratch_t<unsigned long long>(S_BINS, size_t(hist->nbins) + 3, &bins));
     b.part = nullptr;
-    if (b.apart) HG_TRY(scratch_t<double>(S_PART, size_t(b.nchunks) * size_t(np), &b.part));
+    if (b.apart) HG_TRY(scratch_t<double>(S_PART, size_t(b.nchunks) * keep, &b.part));
     // one spare tile slot: two-points-per-lane shapes write a zero sum there
     HG_TRY(scratch_t<double>(S_PARTIALS, size_t(3) * size_t((np + 63) / 64 + 1), &b.partials));
     HG_TRY(scratch_t<double>(S_RES, 8, &b.res));
     HG_TRY(scratch_t<unsigned>(S_FLAGS, 1, &flags));
 
-    HG_TRY(enqueue_generation(n, *cfg, b, s, flags));  // also clears flags
-    HG_TRY(launch_me2_timed(*v, mc_me2_args(n, *cfg, b, flags), s));
     double *staged = d_out ? nullptr : g.pinned + kStaged * (g.ring.fetch_add(1) % kRing);
     if (staged_out) *staged_out = staged;
-    HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, staged, s));
+    if (fused) {
+        if (ev) HG_HIP(heget::launch_events(n, slice_gen_params(n, *cfg), ev_w, ev_y, ev_h, s));
+        HG_TRY(enqueue_fused(n, *cfg, b, d_out, staged, s, ev ? ev_w : b.wout, hist, b.mom, bins));
+        if (events_mom)  // the same points again, for their momenta
+            HG_HIP(heget::launch_gen(n, slice_gen_params(n, *cfg), b.mom, np, b.wfac, nullptr, nullptr, s));
+    } else {
+        // also clears flags and bins
+        HG_TRY(enqueue_generation(n, *cfg, b, s, flags, bins, hist ? hist->nbins + 3 : 0));
+        HG_TRY(launch_me2_timed(*v, mc_me2_args(n, *cfg, b, flags), s));
+        HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, staged, s));
+    }
     if (hist) {
-        HG_HIP(heget::launch_zero_u32(reinterpret_cast<unsigned *>(bins), 2 * (hist->nbins + 2), s));
-        HG_HIP(heget::launch_hist(n, b.mom, np, b.index, b.wout, b.d_count, np, b.res,
-                                  hist->observable, hist->nbins, hist->lo, hist->hi, bins, s));
-        HG_HIP(heget::launch_hist_finish(bins, hist->nbins, b.res, np, hist->host, s));
+        const heget::HistArgs ha{b.mom,    np, b.index, b.wout, b.d_count, np, b.res, hist->observable, hist->nbins,
+                                 hist->lo, hist->hi, bins, np, hist->host};
+        HG_HIP(heget::launch_hist(fused ? 0 : n, ha, s));
     }
     if (ev) {
-        const heget::GenParams gp = slice_gen_params(n, *cfg);
-        HG_HIP(heget::launch_events(n, gp, ev_w, ev_y, ev_h, s));
-        HG_HIP(heget::launch_event_scatter(b.index, b.wout, b.d_count, np, ev_w, s));
+        if (!fused) {
+            HG_HIP(heget::launch_events(n, slice_gen_params(n, *cfg), ev_w, ev_y, ev_h, s));
+            HG_HIP(heget::launch_event_scatter(b.index, b.wout, b.d_count, np, ev_w, s));
+        }
         HG_HIP(hipMemcpyAsync(ev->weight, ev_w, sizeof(double) * size_t(np), hipMemcpyDeviceToHost, s));
         if (ev_y)
             HG_HIP(hipMemcpyAsync(ev->rapidity, ev_y, sizeof(double) * size_t(np),
@@ -923,6 +969,12 @@ heget_status batch_enqueue_branches(int ncfg, const int *n, const heget_config *
         const heget_config &c = cfgs[i];
         const McBufs &b = sb[i].b;
         HG_HIP(hipStreamWaitEvent(si, g.fork, 0));
+        if (runs_fused(n[i], c)) {
+            HG_TRY(enqueue_fused(n[i], c, b, nullptr, staged + kStaged * i, si));
+            HG_HIP(hipEventRecord(g.join[i], si));
+            HG_HIP(hipStreamWaitEvent(s, g.join[i], 0));
+            continue;
+        }
         HG_TRY(enqueue_generation(n[i], c, b, si));
         HG_HIP(heget::launch_me2(*pick_variant(c.prec, n[i], c.npoints / 2), mc_me2_args(n[i], c, b, flags), si));
         HG_TRY(enqueue_reduction(c, b, flags, nullptr, staged + kStaged * i, si));
@@ -1406,6 +1458,7 @@ heget_status heget_xsec_device_noalloc(int n, const heget_config *cfg, heget_res
     ar.base = static_cast<char *>(base);
     carve_static(n, *cfg, *v, ar, b, &flags);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (runs_fused(n, *cfg)) return enqueue_fused(n, *cfg, b, d_out, nullptr, s);
     HG_TRY(enqueue_generation(n, *cfg, b, s, flags));  // also clears flags
     HG_HIP(heget::launch_me2(*v, mc_me2_args(n, *cfg, b, flags), s));
     HG_TRY(enqueue_reduction(*cfg, b, flags, d_out, nullptr, s));

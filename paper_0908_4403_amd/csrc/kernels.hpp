@@ -124,24 +124,46 @@ hipError_t launch_sum_chunks(const double *part, int nchunks, int64_t ld, const 
 
 // Weighted histograms of an event observable (0: largest photon pT, 1:
 // smallest photon-pair Delta R) over the survivors: w[k] of survivor k (point
-// index[k] of mom) goes to bins[0] below lo, bins[1 + b] for bin b of nbins on
-// [lo, hi), bins[nbins + 1] above.  Bins are 64-bit fixed-point integers
-// scaled by 2^(62 - e) where 2^e > res[0] (the sum of all weights), so the sums
-// are exact and independent of the order of the atomic adds; `bins` must be
-// zero at launch.  hist_finish converts them to sum(w) / n_gen per bin.
+// index[k] of mom, *d_count <= points of them; or, for n = 0, of every generated
+// point k < points with the observable in mom[k]) goes to bin 0 below lo, 1 + b
+// for bin b of nbins on [lo, hi), nbins + 1 above, and hist[] receives the bins'
+// sum(w) / n_gen.  Bins are summed as 64-bit fixed-point integers scaled by
+// 2^(62 - e) where 2^e > res[0] (the sum of all weights), so the sums are exact
+// and independent of the order of the atomic adds; bins[nbins + 3] must be zero
+// at launch (GenParams::bins of the call's first kernel).
 constexpr int kHistMaxBins = 4096;
-hipError_t launch_hist(int n, const double *mom, int64_t ld, const int32_t *index, const double *w,
-                       const int64_t *d_count, int64_t max_count, const double *res,
-                       int observable, int nbins, double lo, double hi, unsigned long long *bins,
-                       hipStream_t stream);
-hipError_t launch_hist_finish(const unsigned long long *bins, int nbins, const double *res,
-                              int64_t n_gen, double *hist, hipStream_t stream);
-// Fixed-order compensated reduction of the ceil(*d_count / 64) tile triples
-// into res[0..3] = (sum + compensation, compensation, sum of squares, *d_count)
-// and, if `record` is set, the heget_result record for n_gen generated points;
-// if `host` is set (pinned host memory), res[0..3] and *flags into host[0..4].
-hipError_t launch_final(const double *partials, const int64_t *d_count, int64_t n_gen, double *res,
-                        void *record, const unsigned *flags, double *host, hipStream_t stream);
+struct HistArgs {
+    const double *mom;
+    int64_t ld;
+    const int32_t *index;
+    const double *w;
+    const int64_t *d_count;
+    int64_t points;
+    const double *res;
+    int observable, nbins;
+    double lo, hi;
+    unsigned long long *bins;
+    int64_t n_gen;
+    double *hist;
+};
+hipError_t launch_hist(int n, const HistArgs &a, hipStream_t stream);
+// The whole path up to the partial sums in one kernel (mc_fused.hip), where
+// has_fused says that it is there and pays: per block of 256 generated points a
+// triple and the accepted points, plus kBlockNonfinite if one of their weights
+// is not finite.  coef as Me2Args::coef.  wout, xout (optional): each
+// generated point's weight (0 if cut) and observable.
+constexpr int32_t kBlockNonfinite = 1 << 30;
+bool has_fused(int n, int prec, bool sampled, int64_t points);
+hipError_t launch_fused(int n, int prec, bool sampled, const GenParams &g, double coef, double *partials,
+                        int32_t *block_acc, double *wout, double *xout, int observable, hipStream_t stream);
+// Fixed-order compensated reduction of the partial triples into res[0..3] =
+// (sum + compensation, compensation, sum of squares, accepted points) and, if
+// `record` is set, the heget_result record for n_gen generated points; if
+// `host` is set (pinned host memory), res[0..3] and the status flags into
+// host[0..4].  With d_count: the triples of its ceil(*d_count / 64) tiles and
+// *flags; with block_acc instead: those of launch_fused's blocks.
+hipError_t launch_final(const double *partials, const int64_t *d_count, const int32_t *block_acc, int64_t n_gen,
+                        double *res, void *record, const unsigned *flags, double *host, hipStream_t stream);
 // FMA issue-rate probe: blocks x 256 threads, iters x 128 FMAs per thread into
 // out[blocks * 256] (float for prec 1, double for prec 0); its flop count.
 hipError_t launch_fma_peak(int prec, void *out, int blocks, int iters, hipStream_t stream);

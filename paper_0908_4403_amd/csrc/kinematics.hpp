@@ -250,6 +250,8 @@ struct GenParams {
     int weight_kind;     // 0: write Phi_n (or 0 if cut); 1: write the full non-|M|^2 weight
     unsigned *clear_word;  // if set, zeroed by the generation launch (the call's status flags)
     uint16_t *hel_out;     // if set, the sampled helicity configuration of every point
+    unsigned long long *bins;  // if set, bin_words words zeroed by the launch (a histogram's bins)
+    int bin_words;
 };
 
 // Helicity configuration drawn for `point` in sampling mode (the paper's
@@ -323,6 +325,67 @@ __device__ __forceinline__ double ipow(double x, int e)
         for (int i = 0; i < -e; ++i) r /= x;
     }
     return r;
+}
+
+// Largest photon pT (WHICH = 0), or smallest photon-pair Delta R (1;
+// pseudorapidity and azimuth as in the cuts; both invariant under the
+// longitudinal boost).
+template <int N, int WHICH>
+__device__ __forceinline__ double event_observable(const Vec4 (&k)[N])
+{
+    if constexpr (WHICH == 0) {
+        double m = 0.0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) m = fmax(m, k[j].x * k[j].x + k[j].y * k[j].y);
+        return sqrt(m);
+    } else {
+        double eta[N], phi[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const double pt2 = k[j].x * k[j].x + k[j].y * k[j].y;
+            eta[j] = copysign(fm::log((sqrt(pt2 + k[j].z * k[j].z) + fabs(k[j].z)) / sqrt(pt2)), k[j].z);
+            phi[j] = fm::atan2(k[j].y, k[j].x);
+        }
+        double m = INFINITY;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = i + 1; j < N; ++j) {
+                double dp = fabs(phi[i] - phi[j]);
+                dp = dp > M_PI ? 2.0 * M_PI - dp : dp;
+                const double de = eta[i] - eta[j];
+                m = fmin(m, sqrt(de * de + dp * dp));
+            }
+        return m;
+    }
+}
+
+// Zero the histogram bins of the call, by its first kernel's first block.
+__device__ __forceinline__ void clear_bins(const GenParams &g)
+{
+    if (g.bins && blockIdx.x == 0)
+        for (int b = threadIdx.x; b < g.bin_words; b += static_cast<int>(blockDim.x)) g.bins[b] = 0ull;
+}
+
+// Kinematics and weight of one point in mode MODE, with the cut decision
+// split: the FP32 screen only, giving 1 (pass),
+// 0 (fail) or -1 (undecided: a cut variable within the screen band of its
+// bound), and the frame rapidity for the FP64 decision of undecided points.
+template <int N, int MODE>
+__device__ __forceinline__ int point_setup_screened(const GenParams &g, uint64_t point, Vec4 (&k)[N],
+                                                    double &e_beam, double &w, double &y)
+{
+    const PointKin pk = point_kinematics<MODE>(g, point);
+    rambo<N>(pk.sqrt_shat, g.seed, point, k);
+    const int s = pk.above ? screen_cuts<N>(k, pk.y, g.pt_min, g.eta_max, g.dr_min) : 0;
+    y = pk.y;
+    e_beam = 0.5 * pk.sqrt_shat;
+    const double shat = pk.sqrt_shat * pk.sqrt_shat;
+    if (g.weight_kind == 0)
+        w = g.phase_volume_coef * ipow(shat, N - 2);
+    else
+        w = g.partonic_coef * ipow(shat, N - 3) * pk.fpdf;
+    return s;
 }
 
 }  // namespace heget

@@ -45,25 +45,16 @@ __device__ __forceinline__ PointLoad<N> load_point(const double *__restrict__ mo
     return q;
 }
 
-// The walk and epilogue of one work item: 64 points (one per lane) x one
-// chunk of helicity walks, from inputs already loaded.  `tab` is this wave's
-// LDS photon table (kPhotonFields * N * 64 values of R).  H = 0 selects
-// helicity sampling: one walk per lane with the configuration q.hel (bit j
-// set = photon j has helicity +1) instead of the sum.
-// Output: with kWeighted, `partials` set and one chunk, the tile's (sum,
-// compensation, sum of squares) of |M|^2 * wf (the Monte-Carlo weights of
-// eq. (1)-(2)), and the weight itself at wout[i] when wout is set; otherwise
-// |M|^2 of the chunk at out[chunk * ld_out + i].
-template <typename R, int N, int MB, int H, int CL, bool kWeighted = true, int PS = 0>
-__device__ __forceinline__ void me2_compute(const PointLoad<N> &q, int64_t npts, int64_t tile,
-                                            int chunk, int nchunks, double coef,
-                                            double *__restrict__ out, int64_t ld_out,
-                                            double *__restrict__ partials, double *__restrict__ wout,
-                                            unsigned *__restrict__ flags, R *tab, int lane)
+// |M|^2 (one chunk of helicity walks) of one point per lane, from inputs already
+// loaded.  `tab` is this wave's LDS photon table (kPhotonFields * N * 64 values
+// of R).  H = 0 selects helicity sampling: one walk per lane with the
+// configuration q.hel (bit j set = photon j has helicity +1) instead of the
+// sum.  NaN where the preconditions do not hold.
+template <typename R, int N, int MB, int H, int CL, int PS = 0>
+__device__ __forceinline__ double me2_value(const PointLoad<N> &q, int chunk, int nchunks, double coef, R *tab,
+                                            int lane)
 {
     constexpr bool kTopInLds = N > MB;
-    const int64_t i = tile * 64 + lane;
-    const bool valid = i < npts;
 
     // ---- FP64 set-up: preconditions, power-of-two scale, light-cone photons
     const double E1 = q.x[0], p1x = q.x[1], p1y = q.x[2], p1z = q.x[3];
@@ -127,8 +118,26 @@ __device__ __forceinline__ void me2_compute(const PointLoad<N> &q, int64_t npts,
         const int ppc = kPasses / nchunks;
         s = tree_sum<R, N, MB, H, CL, PS>(in, tab, lane, chunk * ppc, (chunk + 1) * ppc);
     }
-    double me2 = ldexp(coef * (norm / norm_den) * s, 2 * m * (2 - N));
-    if (!ok) me2 = __builtin_nan("");
+    const double me2 = ldexp(coef * (norm / norm_den) * s, 2 * m * (2 - N));
+    return ok ? me2 : __builtin_nan("");
+}
+
+// The walk and epilogue of one work item: 64 points (one per lane) x one
+// chunk of helicity walks.
+// Output: with kWeighted, `partials` set and one chunk, the tile's (sum,
+// compensation, sum of squares) of |M|^2 * wf (the Monte-Carlo weights of
+// eq. (1)-(2)), and the weight itself at wout[i] when wout is set; otherwise
+// |M|^2 of the chunk at out[chunk * ld_out + i].
+template <typename R, int N, int MB, int H, int CL, bool kWeighted = true, int PS = 0>
+__device__ __forceinline__ void me2_compute(const PointLoad<N> &q, int64_t npts, int64_t tile,
+                                            int chunk, int nchunks, double coef,
+                                            double *__restrict__ out, int64_t ld_out,
+                                            double *__restrict__ partials, double *__restrict__ wout,
+                                            unsigned *__restrict__ flags, R *tab, int lane)
+{
+    const int64_t i = tile * 64 + lane;
+    const bool valid = i < npts;
+    const double me2 = me2_value<R, N, MB, H, CL, PS>(q, chunk, nchunks, coef, tab, lane);
     if (kWeighted && partials && nchunks == 1) {
         const double w = valid ? me2 * q.wf : 0.0;
         if (!isfinite(w)) atomicOr(flags, 1u);
