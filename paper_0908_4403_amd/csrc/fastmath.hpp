@@ -7,6 +7,10 @@
 // test can compare them with the C library on many arguments.
 #pragma once
 #include <math.h>
+#include <stdint.h>
+#include <string.h>
+
+#include "fastmath_tables.hpp"
 
 namespace heget {
 namespace fm {
@@ -120,6 +124,62 @@ __host__ __device__ inline double atan2(double y, double x)
     if (swap) ang = 1.5707963267948966 + (6.123233995736766e-17 - ang);  // pi/2 - ang
     if (x < 0.0) ang = 3.141592653589793 + (1.2246467991473532e-16 - ang);  // pi - ang
     return copysign(ang, y);
+}
+
+// The two functions of a photon's random words, through the tables of
+// fastmath_tables.hpp (`tab`: a copy in LDS): about half the instructions of
+// sincospi and log above.  Both within 2 units in the last place.
+
+// Cosine and sine of 2 pi (w + 1/2) 2^-32: the nearest of 128 tabulated directions
+// turned by the remainder t 2^-32 turns, |t| <= 3 2^24, whose sine and
+// cosine - 1 are summed through t^9 and t^8 (the next terms are below 2^-60).
+__host__ __device__ inline void direction(uint32_t w, const PhotonTables &tab, double *cp, double *sp)
+{
+    const uint32_t up = w + (1u << 24), k = up >> 25;
+    const double t = static_cast<double>(static_cast<int32_t>(w - (up & 0xfe000000u))) + tab.shift[k];
+    const double z = t * t;
+    double ps = 0x1.50783487ee782p-283;
+    ps = fma(ps, z, -0x1.32d2cce62bd86p-218);
+    ps = fma(ps, z, 0x1.466bc6775aae2p-154);
+    ps = fma(ps, z, -0x1.4abbce625be53p-91);
+    ps = fma(ps, z, 0x1.921fb54442d18p-30);
+    const double s = ps * t;
+    double pc = 0x1.e1f506891babbp-251;
+    pc = fma(pc, z, -0x1.55d3c7e3cbffap-186);
+    pc = fma(pc, z, 0x1.03c1f081b5ac4p-122);
+    pc = fma(pc, z, -0x1.3bd3cc9be45dep-60);
+    const double c1 = pc * z;  // cosine - 1
+    const Pair e = tab.circle[k];
+    *cp = fma(e.a, c1, fma(-e.b, s, e.a));
+    *sp = fma(e.b, c1, fma(e.a, s, e.b));
+}
+
+// -log of the product of the uniforms (wa + 1/2) 2^-32 and (wb + 1/2) 2^-32, as
+// rounded: the product is 2^e m with m in [1, 2) in bin i of 128, f = m r_i - 1 (one
+// rounding, |f| < 2^-7), and log m = T_i + log(1 + f), summed through f^8.
+__host__ __device__ inline double minus_log_product(uint32_t wa, uint32_t wb, const PhotonTables &tab)
+{
+    const double p = (static_cast<double>(wa) + 0.5) * (static_cast<double>(wb) + 0.5);  // 2^64 times it
+    uint64_t bits;
+    memcpy(&bits, &p, 8);
+    const uint32_t hi = static_cast<uint32_t>(bits >> 32);
+    const uint32_t i = hi >> 13 & 127u;
+    const int e = static_cast<int>(hi >> 20) - (1023 + 64) + static_cast<int>(i >> 6);
+    const uint64_t mbits = (static_cast<uint64_t>((hi & 0xfffffu) | 0x3ff00000u) << 32) | static_cast<uint32_t>(bits);
+    double m;
+    memcpy(&m, &mbits, 8);
+    const Pair t = tab.logs[i];
+    const double f = fma(m, t.a, -1.0);
+    double q = -1.0 / 8.0;
+    q = fma(q, f, 1.0 / 7.0);
+    q = fma(q, f, -1.0 / 6.0);
+    q = fma(q, f, 1.0 / 5.0);
+    q = fma(q, f, -1.0 / 4.0);
+    q = fma(q, f, 1.0 / 3.0);
+    q = fma(q, f, -1.0 / 2.0);
+    const double lm = t.b + fma(f * f, q, f);
+    const double ed = static_cast<double>(e);
+    return -fma(ed, kLn2Hi, fma(ed, kLn2Lo, lm));
 }
 
 // atan(t) for t in [0, 1] in FP32, for screening cut decisions: the odd

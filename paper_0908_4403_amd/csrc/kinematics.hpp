@@ -21,6 +21,18 @@ struct Vec4 {
     double e, x, y, z;
 };
 
+static __constant__ fm::PhotonTables kDevicePhotonTables = fm::kPhotonTables;
+
+// 1/x for positive normal x away from the ends of the range: the hardware
+// estimate and two Newton steps (within an ulp or so, half the instructions of
+// the division).
+__device__ __forceinline__ double recip_pos(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
 // sqrt(x) for positive normal x (every square root of the generator: the
 // arguments are bounded away from zero, overflow and denormals): the
 // hardware estimate of 1/sqrt(x), one Goldschmidt step for the root and its
@@ -55,7 +67,7 @@ __device__ __forceinline__ void conformal_map(double sqrt_s, Vec4 (&k)[N])
         Qz += k[i].z;
     }
     const double M = sqrt_pos(Qe * Qe - Qx * Qx - Qy * Qy - Qz * Qz);
-    const double r = 1.0 / (M * (M + Qe));
+    const double r = recip_pos(M * (M + Qe));
     const double inv_m = (M + Qe) * r;
     const double bx = -Qx * inv_m, by = -Qy * inv_m, bz = -Qz * inv_m;
     const double x = sqrt_s * inv_m;
@@ -87,7 +99,7 @@ __device__ __forceinline__ void rebalance(double sqrt_s, Vec4 (&k)[N])
         Qy += k[i].y;
         Qz += k[i].z;
     }
-    const double inv = 1.0 / sqrt_s;
+    const double inv = recip_pos(sqrt_s);
     const double x = 1.0 - (Qe - sqrt_s) * inv;
     const double bx = -Qx * inv, by = -Qy * inv, bz = -Qz * inv;
 #pragma unroll
@@ -100,20 +112,32 @@ __device__ __forceinline__ void rebalance(double sqrt_s, Vec4 (&k)[N])
     }
 }
 
-// Photon momenta of point `point`: four uniforms from stream 0, block i, for photon i.
+// The tables of the photons' functions in LDS, copied by the whole workgroup
+// (256 threads) and read after its next barrier.
+__device__ __forceinline__ void load_photon_tables(fm::PhotonTables &t)
+{
+    constexpr int kPairs = sizeof(fm::PhotonTables) / sizeof(fm::Pair);
+    static_assert(kPairs * sizeof(fm::Pair) == sizeof(fm::PhotonTables));
+    const fm::Pair *from = reinterpret_cast<const fm::Pair *>(&kDevicePhotonTables);
+    for (int i = threadIdx.x; i < kPairs; i += 256) reinterpret_cast<fm::Pair *>(&t)[i] = from[i];
+}
+
+// Photon momenta of point `point`: the four words of stream 0, block i, give
+// photon i its cos theta, azimuth and (two) energy.
 template <int N>
-__device__ __forceinline__ void rambo(double sqrt_s, uint64_t seed, uint64_t point, Vec4 (&k)[N])
+__device__ __forceinline__ void rambo(double sqrt_s, uint64_t seed, uint64_t point, const fm::PhotonTables &tab,
+                                      Vec4 (&k)[N])
 {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        double u[4];
-        uniform_quad(seed, point, static_cast<uint32_t>(i), 0u, u);
-        const double ucos = u[0], uphi = u[1], ue1 = u[2], ue2 = u[3];
-        const double c = 2.0 * ucos - 1.0;
+        const Words4 r = philox4x32_10(static_cast<uint32_t>(point), static_cast<uint32_t>(point >> 32),
+                                       static_cast<uint32_t>(i), 0u, static_cast<uint32_t>(seed),
+                                       static_cast<uint32_t>(seed >> 32));
+        const double c = fma(static_cast<double>(r.w0), 0x1.0p-31, 0x1.0p-32 - 1.0);  // 2 (w + 1/2) 2^-32 - 1, exact
         const double s = sqrt_pos(1.0 - c * c);
         double sf, cf;
-        fm::sincospi(2.0 * uphi, &sf, &cf);  // azimuth 2 pi uphi
-        const double e = -fm::log(ue1 * ue2);
+        fm::direction(r.w1, tab, &cf, &sf);
+        const double e = fm::minus_log_product(r.w2, r.w3, tab);
         k[i] = {e, e * s * cf, e * s * sf, e * c};
     }
     conformal_map<N>(sqrt_s, k);
@@ -372,11 +396,12 @@ __device__ __forceinline__ void clear_bins(const GenParams &g)
 // 0 (fail) or -1 (undecided: a cut variable within the screen band of its
 // bound), and the frame rapidity for the FP64 decision of undecided points.
 template <int N, int MODE>
-__device__ __forceinline__ int point_setup_screened(const GenParams &g, uint64_t point, Vec4 (&k)[N],
+__device__ __forceinline__ int point_setup_screened(const GenParams &g, uint64_t point,
+                                                    const fm::PhotonTables &tab, Vec4 (&k)[N],
                                                     double &e_beam, double &w, double &y)
 {
     const PointKin pk = point_kinematics<MODE>(g, point);
-    rambo<N>(pk.sqrt_shat, g.seed, point, k);
+    rambo<N>(pk.sqrt_shat, g.seed, point, tab, k);
     const int s = pk.above ? screen_cuts<N>(k, pk.y, g.pt_min, g.eta_max, g.dr_min) : 0;
     y = pk.y;
     e_beam = 0.5 * pk.sqrt_shat;

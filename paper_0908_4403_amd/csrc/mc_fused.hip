@@ -47,14 +47,17 @@ fused_kernel(GenParams g, double coef, double *__restrict__ partials, int32_t *_
     constexpr int PS = N >= 5 ? 2 : 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    __shared__ fm::PhotonTables tab;
+    load_photon_tables(tab);
     clear_bins(g);
+    __syncthreads();
     bool acc = false;
     double w = 0.0;
     if (i < g.npoints) {
         const uint64_t point = static_cast<uint64_t>(g.first + i);
         Vec4 k[N];
         double e, wf, y;
-        int s = point_setup_screened<N, MODE>(g, point, k, e, wf, y);
+        int s = point_setup_screened<N, MODE>(g, point, tab, k, e, wf, y);
         if (s < 0) s = pass_cuts_fp64<N>(k, y, g.pt_min, g.eta_max, g.dr_min) ? 1 : 0;
         acc = s == 1;
         PointLoad<N> q;

@@ -16,25 +16,29 @@
 
 namespace heget {
 
-// SoA rows of one point: quark momenta (E, 0, 0, +-E), then the photons.
+// SoA rows of one point: quark momenta (E, 0, 0, +-E), then the photons.  The
+// row of the workgroup's first point is uniform (scalar address arithmetic), a
+// lane adds its place in the workgroup.
 template <int N>
-__device__ __forceinline__ void store_point(double *__restrict__ mom, int64_t ld, int64_t col,
-                                            double e, const Vec4 (&k)[N])
+__device__ __forceinline__ void store_point(double *__restrict__ mom, int64_t ld, double e, const Vec4 (&k)[N])
 {
-    mom[0 * ld + col] = e;
-    mom[1 * ld + col] = 0.0;
-    mom[2 * ld + col] = 0.0;
-    mom[3 * ld + col] = e;
-    mom[4 * ld + col] = e;
-    mom[5 * ld + col] = 0.0;
-    mom[6 * ld + col] = 0.0;
-    mom[7 * ld + col] = -e;
+    double *block = mom + static_cast<int64_t>(blockIdx.x) * 256;
+    const uint32_t t = threadIdx.x;
+    auto put = [&](int row, double v) { (block + row * ld)[t] = v; };
+    put(0, e);
+    put(1, 0.0);
+    put(2, 0.0);
+    put(3, e);
+    put(4, e);
+    put(5, 0.0);
+    put(6, 0.0);
+    put(7, -e);
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        mom[(8 + 4 * j) * ld + col] = k[j].e;
-        mom[(9 + 4 * j) * ld + col] = k[j].x;
-        mom[(10 + 4 * j) * ld + col] = k[j].y;
-        mom[(11 + 4 * j) * ld + col] = k[j].z;
+        put(8 + 4 * j, k[j].e);
+        put(9 + 4 * j, k[j].x);
+        put(10 + 4 * j, k[j].y);
+        put(11 + 4 * j, k[j].z);
     }
 }
 
@@ -45,9 +49,12 @@ __global__ void __launch_bounds__(256)
 gen_kernel(GenParams g, double *__restrict__ mom, int64_t ld, double *__restrict__ wout,
            uint8_t *__restrict__ flag, int32_t *__restrict__ block_count)
 {
+    __shared__ fm::PhotonTables tab;
+    load_photon_tables(tab);
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (g.clear_word && i == 0) *g.clear_word = 0u;
     clear_bins(g);
+    __syncthreads();
     bool acc = false;
     if (i < g.npoints) {
         double w, y;
@@ -55,8 +62,8 @@ gen_kernel(GenParams g, double *__restrict__ mom, int64_t ld, double *__restrict
         {
             Vec4 k[N];
             double e;
-            s = point_setup_screened<N, MODE>(g, static_cast<uint64_t>(g.first + i), k, e, w, y);
-            store_point<N>(mom, ld, i, e, k);
+            s = point_setup_screened<N, MODE>(g, static_cast<uint64_t>(g.first + i), tab, k, e, w, y);
+            store_point<N>(mom, ld, e, k);
         }
         if (s < 0) {
             // Rare: decide in FP64 from the momenta just stored.  The row
