@@ -13,7 +13,7 @@ constexpr Me2Variant lanes_variant()
 
 // (waves on a wave's points, waves per SIMD): see me2_lanes.hpp
 extern const Me2Variant kShapesLanes[] = {
-    lanes_variant<float, 6, 1, 2>(),  lanes_variant<float, 7, 1, 2>(),  lanes_variant<float, 8, 2, 3>(),
+    lanes_variant<float, 6, 2, 4>(),  lanes_variant<float, 7, 2, 4>(),  lanes_variant<float, 8, 2, 4>(),
     lanes_variant<double, 6, 2, 2>(), lanes_variant<double, 7, 2, 2>(), lanes_variant<double, 8, 2, 2>(),
 };
 extern const int kShapesLanesCount = sizeof(kShapesLanes) / sizeof(Me2Variant);

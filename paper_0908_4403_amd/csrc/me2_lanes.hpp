@@ -17,39 +17,39 @@
 // 2 .. n-1 have the bits of s (photons 0 and 1 run over the lane's four FP64
 // accumulators), and the currents pass between lanes through the wave's LDS.
 //
-// Phases, each reading what the phase before wrote:
+// Phases, each reading what the phase before wrote (two waves share a point's
+// LDS, take the rounds of a phase in turn and meet at a barrier per phase):
 //   1. lane s < n: photon s (scaled light-cone momentum, both vertex blocks);
 //   2. propagators of all sets of up to K - 1 (v-bar end), n - K - 1 (u end);
-//   3. J level by level up to K - 1, then R up to n - K - 1: a task is one
-//      (set, helicities of the set), 2^m consecutive lanes share a set;
+//   3. J level by level up to K - 1, then R up to n - K - 1: a task is one set
+//      with the helicities of all its photons but the last, whose two a lane
+//      forms together (they share the children and blocks that they read);
 //   4. propagators of the sets of K photons;
-//   5. per chunk of sets A: the 2^K values of every J(A) and the 2^(n-K) of
-//      every W(B) go to an LDS buffer, and the lanes contract them, each for
-//      its four configurations.
-// Sets A are walked grouped by which of photons 0 and 1 they hold, so that
-// the pattern of a lane's four contractions is known at compile time.
+//   5. per chunk of four sets A, the waves taking every other chunk through an
+//      LDS buffer of their own: the 2^K values of every J(A) and the 2^(n-K) of
+//      every W(B) go to the buffer, and the lanes contract them, each for its
+//      four configurations.  Within a wave LDS operations execute in order, so
+//      no barrier is met; the waves add their accumulators at the end.
+// Sets A are walked grouped by which of photons 0 and 1 they hold, so that the
+// pattern of a lane's four contractions is known at compile time.  Where the J
+// (or the W) of a chunk would leave lanes idle (n = 8) one round forms both:
+// a row's step is a column's with the halves of the vertex block swapped, so the
+// u end's lanes read swapped copies of the blocks and a propagator of unity.
+// All LDS addresses of a lane come from tables made at compile time.
 //
-// With W = 1 a workgroup is one wave: the LDS operations of a wave execute in
-// order, so a phase ends with a compiler fence and no barrier, and phase 5
-// fills one of two buffers while it contracts the other.  With W = 2 two waves
-// share the same points (and LDS): they take the rounds of a phase and the
-// chunks in turn, each through a buffer of its own, meet at a barrier per
-// phase and add their accumulators at the end.
-//
-// What bounds it: VALU issue, 7 000 (FP32) and 6 600 (FP64) instructions per
-// point and wave at n = 8 (counters: 0.23 per clock and SIMD in FP32, where
-// 0.25 is the rate of one wave; LDS busy 48% of the clocks).  LDS (20 KiB per
-// wave in FP32, 40 in FP64) allows two waves per SIMD in FP32 but one in FP64,
-// which stood still 41% of the time: hence W = 2 there (points/s, W = 1 -> 2:
-// n = 8 3.95e7 -> 5.09e7, n = 7 1.14e8 -> 1.48e8, n = 6 3.66e8 -> 4.23e8).  In
-// FP32 a third wave per SIMD gains at n = 8 only (8.08e7 -> 8.37e7; at 2053
-// points 46.8 -> 34.6 us); at n = 7 it spills, at n = 6 both forms run alike.
-// Measured (points/s, one-lane-per-point kernel before -> this one; 524 288,
-// 200 003 and 111 040 points at 1.5 TeV): FP32 n = 6 3.3e8 -> 7.6e8, n = 7
-// 4.3e7 -> 2.3e8, n = 8 6.4e6 -> 8.4e7; FP64 n = 6 9.7e7 -> 4.8e8, n = 7
-// 8.9e6 -> 1.5e8, n = 8 1.2e6 -> 5.1e7.  Every FP32 value is formed by the
-// same operations in the same order, so FP32 results have the same bits (up to
-// the order in which W = 2 adds the sets).
+// What bounds it: in FP32 VALU issue (n = 8: 6 900 instructions per point; at
+// four waves per SIMD the counters show the issue slots full, LDS busy half of
+// the clocks), in FP64 the LDS reads, 16 bytes each and two per value, of two
+// waves per SIMD (40 KiB of LDS per workgroup; more waves through a shared
+// buffer and barriers ran 5% slower).
+// Measured (us; helicities by one lane per point -> one task per value and one
+// to two waves -> this form; 131 101, 65 537 and 20 001 points): FP32 n = 6
+// 397 -> 191 -> 154, n = 7 1 530 -> 284 -> 243, n = 8 3 100 -> 249 -> 220; FP64
+// n = 6 1 350 -> 281 -> 272, n = 7 7 400 -> 447 -> 428, n = 8 16 700 -> 395 ->
+// 381.  At 2053 points FP32: n = 6 11.0 -> 8.4, n = 7 19.4 -> 14.6, n = 8 32.0 ->
+// 28.7.  Every FP32 value is formed by the same operations in the same order in
+// all of these, so FP32 results have the same bits (up to the order in which the
+// waves add the sets).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -64,17 +64,31 @@
 namespace heget {
 namespace lanes {
 
-// Fixed numbers of the split for n photons with W waves on a wave's points.
+// Fixed numbers of the split for n photons with W = 2 waves on a workgroup's points
+// (one wave, two chunk buffers in turn, was slower at every size: FP32 n = 7, 65 537
+// points 276 us instead of 243, 2053 points 18.2 instead of 14.6).
 template <int N, int WAVES>
 struct Split {
     static constexpr int W = WAVES;
     static constexpr int K = (N + 1) / 2, U = N - K;
     static constexpr int S = 1 << (N - 2), P = 64 / S;
     static constexpr int kSets = binomial(N, K);
-    // sets per chunk: the values of J of a chunk fill whole rounds of S lanes
-    static constexpr int C = N <= 6 && W == 2 ? 2 : 4;
+    // first walked set that holds photon 0 only, 1 only, neither of the two
+    static constexpr int kFrom1 = binomial(N - 2, K - 2), kFrom2 = kFrom1 + binomial(N - 2, K - 1),
+                         kFrom0 = kFrom2 + binomial(N - 2, K - 1);
+    // of photons 0 and 1, those in the set of walking slot `slot`
+    static constexpr uint32_t held(int slot) { return slot < kFrom1 ? 3u : slot < kFrom2 ? 1u : slot < kFrom0 ? 2u : 0u; }
+    // sets per chunk: the values of J and W of a chunk fill whole rounds of S lanes
+    static constexpr int C = 4;
     static constexpr int kChunks = (kSets + C - 1) / C;
     static constexpr int kSlots = kChunks * C;
+    // a lane forms a set's values for both helicities of its last photon where
+    // that fills the rounds; J and W share a round where each alone would not
+    static constexpr bool kMixed = (C << (K - 1)) % S != 0;
+    static constexpr int kOutJ = 2, kOutW = kMixed || (C << (U - 1)) % S == 0 ? 2 : 1;
+    static constexpr int kTasksJ = (C << K) / kOutJ, kTasksW = (C << U) / kOutW;
+    static constexpr int kRounds = (kTasksJ + kTasksW) / S;  // of a chunk
+    static_assert((kTasksJ + kTasksW) % S == 0 && (kMixed ? K == U && kRounds == 1 : kTasksJ % S == 0));
     static constexpr int props_j()
     {
         int r = 0;
@@ -90,15 +104,17 @@ struct Split {
     static constexpr int level_size(int l) { return binomial(N, l) << l; }
     static constexpr int max2(int a, int b) { return a > b ? a : b; }
     // LDS regions of one point, in entries of four values (16 bytes per plane)
-    static constexpr int kChunkJ = C << K, kChunkW = C << U, kChunk = kChunkJ + kChunkW;
+    static constexpr int kChunkJ = C << K, kChunk = kChunkJ + (C << U);
     // level 2 where it does not stay (of the v-bar end, then of the u end)
     static constexpr int lower() { return K - 1 > 2 ? level_size(2) : 0; }
     static constexpr int kJ = 0;                               // J of level K - 1
     static constexpr int kR = kJ + level_size(K - 1);          // R of level n - K - 1
-    static constexpr int kT = kR + level_size(U - 1);          // a zero momentum, level 2, chunk buffer 0
-    static constexpr int kT2 = kT + max2(lower(), kChunk);     // u-end propagators, level 1, chunk buffer 1
-    static constexpr int kProp = kT2 + max2(props_r() + level_size(1), kChunk);  // v-bar-end propagators
-    static constexpr int kRec = kProp + max2(props_j(), kSets);  // then those of level K
+    static constexpr int kT = kR + level_size(U - 1);          // a zero momentum, level 2; then a chunk per wave
+    static constexpr int kT2 = kT + max2(lower(), 1);          // u-end propagators, level 1
+    static constexpr int kProp = max2(kT2 + props_r() + level_size(1), kT + W * kChunk);  // v-bar-end propagators
+    static constexpr int kSwap = kProp + kSlots;               // then those of level K, and where J and W share a
+    static constexpr int kOne = kSwap + 2 * N;                 // round the blocks as a row takes them, and unity
+    static constexpr int kRec = kProp + max2(props_j(), kMixed ? kSlots + 2 * N + 1 : kSlots);
     static constexpr int kRecSize = 3;                         // photon: block of helicity -, +, momentum
     // LDS of a point: with four or more points per wave an odd multiple of eight
     // entries, half the 256 bytes that the banks span, so that two points' reads
@@ -108,6 +124,7 @@ struct Split {
     // sixteen lie between)
     static constexpr int kUsed = kRec + kRecSize * N;
     static constexpr int kEntries = P >= 4 ? (kUsed + 7) / 16 * 16 + 8 : kUsed;
+    static_assert(kEntries * P * 16 <= 65536, "byte offsets of a plane are 16 bits");
     // entry of level l of the v-bar end or (row) the u end
     static constexpr int level_at(bool row, int l)
     {
@@ -120,36 +137,25 @@ struct Split {
         for (int i = 1; i < l; ++i) a += binomial(N, i);
         return a;
     }
+    // rounds of level l (2 or more), two helicity configurations per lane
+    static constexpr int level_rounds(int l) { return (level_size(l) / 2 + S - 1) / S; }
 };
 
-// Index tables (byte offsets within a region, at 16 bytes per entry), built
-// at compile time.
+// Byte offsets into a plane of the workgroup's LDS, worked out for each of the
+// 64 lanes at compile time (lane l of a wave: point l / S, lane l % S of it).
+struct alignas(16) LaneRow {
+    uint32_t w[4];  // per photon of the lane's set: the child's value | the vertex block's << 16
+};
+
 template <int N, int W>
 struct alignas(16) Tables {
     using L = Split<N, W>;
-    uint32_t con[L::kSlots][L::S];  // lane s: J entry | W entry << 16 within the chunk's set
-    uint32_t mj[L::kSlots][4];      // per photon of A: J(A \ j) at level K - 1 | record << 16
-    uint32_t mw[L::kSlots][4];      // per photon of B: R(B \ b) at level U - 1 | record << 16
-    uint32_t lev[3][56][4];         // levels 2, 3 (index l - 1): as mj, for sets in increasing order
-    uint16_t prop[256][4];          // photon momenta of each propagator task (offsets from the point's LDS)
-    uint16_t set_of[L::kSlots];     // the sets A in walking order (padded with the last one)
+    LaneRow build[L::kChunks][L::kRounds][64];  // rounds of a chunk: its J, then its W
+    LaneRow lev[2][5][64];                      // rounds of levels 2 and 3 (index l - 2; both ends)
+    LaneRow con[L::kChunks][64];                // per set of a chunk: the lane's J | W << 16 in the chunk buffer
+    uint16_t prop[256][4];                      // photon momenta of each propagator task (from the point's LDS)
+    uint16_t set_of[L::kSlots];                 // the sets A in walking order (padded with the last one)
 };
-
-// Sets A of K photons: those holding photons 0 and 1, 0 only, 1 only, neither.
-template <int N>
-constexpr uint32_t walk_set(int i)
-{
-    constexpr int K = (N + 1) / 2;
-    constexpr uint32_t kPattern[4] = {3u, 1u, 2u, 0u};
-    int at = 0;
-    for (int t = 0; t < 4; ++t)
-        for (uint32_t m = 1; m < (1u << N); ++m)
-            if (__builtin_popcount(m) == K && (m & 3u) == kPattern[t]) {
-                if (at == i) return m;
-                ++at;
-            }
-    return 0u;
-}
 
 // Bits of h at the positions of `set`, packed to the bottom.
 constexpr uint32_t pack_bits(uint32_t h, uint32_t set)
@@ -161,18 +167,32 @@ constexpr uint32_t pack_bits(uint32_t h, uint32_t set)
     return r;
 }
 
-// Per photon of `set`: entry of set \ photon on the level below | record << 16.
+// h without bit p.
+constexpr uint32_t without_bit(uint32_t h, int p)
+{
+    return (h & ((1u << p) - 1u)) | ((h >> (p + 1)) << p);
+}
+
+// Row of the lane of point `pt` that forms the values of `set` for the helicities
+// f of its photons but (out = 2) the last, from the level below at entry `from`.
 template <int N, int W>
-constexpr void child_entries(uint32_t set, uint32_t (&out)[4])
+constexpr LaneRow lane_row(const uint8_t (&rank)[256], uint32_t set, uint32_t f, int out, int from, int pt,
+                           bool swapped = false)
 {
     using L = Split<N, W>;
+    LaneRow r{};
     const int l = __builtin_popcount(set);
-    for (int p = 0; p < 4; ++p) out[p] = 0;
-    for (int p = 0; p < l; ++p) {
-        const int j = nth_bit(set, p);
-        const uint32_t e = static_cast<uint32_t>(subset_rank<N>(set & ~(1u << j))) << (l - 1);
-        out[p] = e * 16u | static_cast<uint32_t>(L::kRecSize * j * 16) << 16;
+    int p = 0;
+    for (int j = 0; j < N; ++j) {
+        if (!(set >> j & 1u)) continue;
+        const int child = from + (rank[set & ~(1u << j)] << (l - 1)) + static_cast<int>(without_bit(f, p));
+        const int e = out == 2 && p == l - 1 ? 0 : static_cast<int>(f >> p & 1u);
+        const int block = swapped ? L::kSwap + 2 * j + e : L::kRec + L::kRecSize * j + e;
+        r.w[p] = static_cast<uint32_t>((pt * L::kEntries + child) * 16) |
+                 static_cast<uint32_t>((pt * L::kEntries + block) * 16) << 16;
+        ++p;
     }
+    return r;
 }
 
 template <int N, int W>
@@ -189,25 +209,50 @@ constexpr Tables<N, W> make_tables()
 {
     using L = Split<N, W>;
     Tables<N, W> t{};
-    for (int i = 0; i < L::kSlots; ++i) {
-        const uint32_t A = walk_set<N>(i < L::kSets ? i : L::kSets - 1);
-        const uint32_t B = ((1u << N) - 1u) & ~A;
-        t.set_of[i] = static_cast<uint16_t>(A);
-        child_entries<N, W>(A, t.mj[i]);
-        child_entries<N, W>(B, t.mw[i]);
-        for (int s = 0; s < L::S; ++s) {
-            const uint32_t h = static_cast<uint32_t>(s) << 2;
-            t.con[i][s] = pack_bits(h, A) * 16u | (pack_bits(h, B) * 16u) << 16;
-        }
+    uint8_t rank[256] = {}, of_rank[N + 1][70] = {};
+    int seen[N + 1] = {};
+    for (uint32_t m = 1; m < (1u << N); ++m) {  // as subset_rank
+        const int l = __builtin_popcount(m);
+        of_rank[l][seen[l]] = static_cast<uint8_t>(m);
+        rank[m] = static_cast<uint8_t>(seen[l]++);
     }
-    for (int l = 2; l <= 3; ++l)
-        if (l <= L::K - 1) {
-            int r = 0;
-            for (uint32_t m = 1; m < (1u << N); ++m)
-                if (__builtin_popcount(m) == l) child_entries<N, W>(m, t.lev[l - 1][r++]);
-        }
-    // propagator tasks: v-bar end levels 1 .. K - 1, u end 1 .. U - 1, level K
+    // sets A of K photons: those holding photons 0 and 1, 0 only, 1 only, neither
     int at = 0;
+    while (at < L::kSets) {
+        const uint32_t held = L::held(at);
+        for (uint32_t m = 1; m < (1u << N); ++m)
+            if (__builtin_popcount(m) == L::K && (m & 3u) == held) t.set_of[at++] = static_cast<uint16_t>(m);
+    }
+    for (; at < L::kSlots; ++at) t.set_of[at] = t.set_of[L::kSets - 1];
+    constexpr uint32_t kAll = (1u << N) - 1u;
+    for (int lane = 0; lane < 64; ++lane) {
+        const int s = lane % L::S, pt = lane / L::S;
+        for (int c = 0; c < L::kChunks; ++c)
+            for (int r = 0; r < L::kRounds; ++r) {
+                const bool row = r * L::S + s >= L::kTasksJ;
+                const int lv = row ? L::U : L::K, out = row ? L::kOutW : L::kOutJ, h = (1 << lv) / out;
+                const int task = r * L::S + s - (row ? L::kTasksJ : 0);
+                const uint32_t A = t.set_of[c * L::C + task / h];
+                t.build[c][r][lane] = lane_row<N, W>(rank, row ? kAll & ~A : A, static_cast<uint32_t>(task % h), out,
+                                                     row ? L::kR : L::kJ, pt, row && L::kMixed);
+            }
+        for (int i = 0; i < L::kSlots; ++i) {
+            const uint32_t A = t.set_of[i], h = static_cast<uint32_t>(s) << 2;
+            const int base = pt * L::kEntries + L::kT + i / L::C % W * L::kChunk, in = i % L::C;
+            t.con[i / L::C][lane].w[in] = (base + (in << L::K) + pack_bits(h, A)) * 16u |
+                             ((base + L::kChunkJ + (in << L::U) + pack_bits(h, kAll & ~A)) * 16u) << 16;
+        }
+        for (int l = 2; l <= 3; ++l)
+            if (l <= L::K - 1)
+                for (int r = 0; r < L::level_rounds(l); ++r) {
+                    // lanes past the last task repeat the last set
+                    const int h = 1 << (l - 1), task = r * L::S + s, last = binomial(N, l) - 1;
+                    t.lev[l - 2][r][lane] = lane_row<N, W>(rank, of_rank[l][task / h < last ? task / h : last],
+                                                           static_cast<uint32_t>(task % h), 2, L::level_at(false, l - 1), pt);
+                }
+    }
+    // propagator tasks: v-bar end levels 1 .. K - 1, u end 1 .. U - 1, level K
+    at = 0;
     for (int end = 0; end < 2; ++end)
         for (int l = 1; l < (end == 0 ? L::K : L::U); ++l)
             for (uint32_t m = 1; m < (1u << N); ++m)
@@ -236,9 +281,11 @@ __device__ __forceinline__ TabPtr<N, W> fresh_tables()
     return t;
 }
 
-__device__ __forceinline__ u32x4 row4(const HEGET_CONST_AS uint32_t *p)
+// Lane `lane`'s row of a table row of the wave: from a scalar address.
+__device__ __forceinline__ u32x4 row4(const HEGET_CONST_AS LaneRow *wave_row, int lane)
 {
-    return *(const HEGET_CONST_AS u32x4 *)p;
+    asm volatile("" : "+s"(wave_row));
+    return *(const HEGET_CONST_AS u32x4 *)(wave_row + static_cast<uint32_t>(lane));
 }
 
 // Four values of one LDS entry.  FP64 entries lie in two planes of 16 bytes
@@ -279,23 +326,14 @@ __device__ __forceinline__ void put(char *p, const Quad<double> &q)
     *reinterpret_cast<f64x2 *>(p + PLANE) = f64x2{q.c, q.d};
 }
 
-// End of a phase: what the point's lanes wrote to LDS is read by other lanes
-// after it.  The LDS unit executes one wave's operations in order, so within a
-// wave only the compiler has to keep that order; two waves meet at a barrier.
+// What a lane of this wave wrote to LDS is read by others of the wave after it:
+// the LDS unit executes one wave's operations in order, so only the compiler
+// has to keep that order.
 __device__ __forceinline__ void wave_phase_end()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
-template <int W>
-__device__ __forceinline__ void phase_end()
-{
-    if constexpr (W == 1)
-        wave_phase_end();
-    else
-        __syncthreads();
 }
 
 // Sum (or product) of v over the S lanes of a point, left in every lane.
@@ -356,10 +394,28 @@ __device__ __forceinline__ Quad<R> propagated(const Quad<R> &P, const Quad<R> &s
     return o;
 }
 
-// Entry offset of helicity bits e without bit p.
-__device__ __forceinline__ uint32_t drop_bit(uint32_t e, int p)
+// sum_p V_p c(set \ p) of a set of LV photons for OUT helicity configurations
+// (rows: c V): those of the lane's table row, and (OUT = 2) of the last photon
+// both.  The pair shares all vertex blocks but the last photon's, which are the
+// same four values in another order, and that photon's child: 2 LV + (2 LV - 1)
+// reads from LDS instead of 4 LV.
+template <typename R, int LV, bool ROW, int OUT, int PLANE>
+__device__ __forceinline__ void vertices(const char *lds_all, const u32x4 &row, Quad<R> (&sum)[OUT])
 {
-    return (e & ((1u << p) - 1u)) | ((e >> (p + 1)) << p);
+    static_for<0, LV>([&](auto pi) {
+        constexpr int p = decltype(pi)::value;
+        const char *child = lds_all + (row[p] & 0xffffu);
+        const Quad<R> v = get<PLANE>(lds_all + (row[p] >> 16), R());
+        if constexpr (OUT == 2 && p == LV - 1) {
+            const Quad<R> c = get<PLANE>(child, R());
+            vertex<ROW, p == 0>(v, c, sum[0]);
+            vertex<ROW, p == 0>(Quad<R>{v.c, -v.d, v.a, -v.b}, c, sum[1]);
+        } else {
+#pragma unroll
+            for (int o = 0; o < OUT; ++o)
+                vertex<ROW, p == 0>(v, get<PLANE>(child + o * (16 << (LV - 2)), R()), sum[o]);
+        }
+    });
 }
 
 // Propagators of the COUNT tasks from FIRST in the table on, to entry `AT`:
@@ -394,119 +450,111 @@ __device__ __forceinline__ void propagators(char *lds, int s, int first, R base_
     }
 }
 
-// Level LV of one end (ROW: the u end) from the level below.
-template <typename R, int N, int W, int LV, bool ROW, int PLANE>
-__device__ __forceinline__ void build_level(char *lds, int s, int first)
+// Level 1 of one end (ROW: the u end).
+template <typename R, int N, int W, bool ROW, int PLANE>
+__device__ __forceinline__ void build_first(char *lds, int s, int first)
 {
     using L = Split<N, W>;
-    constexpr int S = L::S, H = 1 << LV, kTasks = L::level_size(LV);
-    constexpr int FROM = L::level_at(ROW, LV - 1), TO = L::level_at(ROW, LV);
-    constexpr int PR = (ROW ? L::kT2 : L::kProp) + L::props_below(LV);
+    constexpr int S = L::S, TO = L::level_at(ROW, 1), PR = ROW ? L::kT2 : L::kProp;
+    static_assert(2 * N <= S, "one round");
+    if (first != 0) return;
+    // lanes past the last task repeat the last photon (same values, same place)
+    const int photon = s / 2 < N ? s / 2 : N - 1, e = s & 1;
+    const Quad<R> P = get<PLANE>(lds + (PR + photon) * 16, R());
+    const Quad<R> v = get<PLANE>(lds + (L::kRec + L::kRecSize * photon + e) * 16, R());
+    Quad<R> o;
+    if constexpr (!ROW)  // V (1, 0) = (1, gamma)
+        o = {fma(-P.c, v.c, fma(P.d, v.d, P.a)), -fma(P.c, v.d, P.d * v.c), fma(P.b, v.c, -P.c),
+             fma(P.b, v.d, P.d)};
+    else  // (gamma, -1)
+        o = {fma(v.c, P.a, P.c), fma(v.d, P.a, -P.d), -fma(v.c, P.c, fma(-v.d, P.d, P.b)),
+             -fma(v.c, P.d, v.d * P.c)};
+    put<PLANE>(lds + (TO + 2 * photon + e) * 16, o);
+}
+
+// Level LV (2 or more) of one end (ROW: the u end) from the level below.
+template <typename R, int N, int W, int LV, bool ROW, int PLANE>
+__device__ __forceinline__ void build_level(char *lds_all, char *lds, int lane, int first)
+{
+    using L = Split<N, W>;
+    constexpr int S = L::S, H = 1 << (LV - 1), kTasks = L::level_size(LV) / 2, kRounds = L::level_rounds(LV);
+    constexpr int TO = L::level_at(ROW, LV), PR = (ROW ? L::kT2 : L::kProp) + L::props_below(LV);
+    static_assert(!ROW || L::level_at(true, LV - 1) == L::level_at(false, LV - 1), "the ends share their table");
     const TabPtr<N, W> tabs = fresh_tables<N, W>();
-    const uint32_t e = static_cast<uint32_t>(s) & (H - 1);
-    uint32_t child[LV], block[LV];
-#pragma unroll
-    for (int p = 0; p < LV; ++p) {
-        child[p] = drop_bit(e, p) * 16u;
-        block[p] = (e >> p & 1u) * 16u;
-    }
-    constexpr int kRounds = (kTasks + S - 1) / S;
+    const int s = lane % S;
 #pragma unroll
     for (int i = 0; i < (kRounds + W - 1) / W; ++i) {
         const int r = i * W + first;
         if (kRounds % W != 0 && r >= kRounds) break;
         // lanes past the last task repeat the last set (same values, same place)
-        const int t = r * S + s;
-        int set = t >> LV;
+        int set = (r * S + s) / H;
         if (kTasks % S != 0) set = set < binomial(N, LV) ? set : binomial(N, LV) - 1;
         const Quad<R> P = get<PLANE>(lds + (PR + set) * 16, R());
-        Quad<R> o;
-        if constexpr (LV == 1) {
-            const Quad<R> v = get<PLANE>(lds + L::kRec * 16 + set * (L::kRecSize * 16) + block[0], R());
-            if constexpr (!ROW)  // V (1, 0) = (1, gamma)
-                o = {fma(-P.c, v.c, fma(P.d, v.d, P.a)), -fma(P.c, v.d, P.d * v.c), fma(P.b, v.c, -P.c),
-                     fma(P.b, v.d, P.d)};
-            else  // (gamma, -1)
-                o = {fma(v.c, P.a, P.c), fma(v.d, P.a, -P.d), -fma(v.c, P.c, fma(-v.d, P.d, P.b)),
-                     -fma(v.c, P.d, v.d * P.c)};
-        } else {
-            const u32x4 tab = row4(tabs->lev[LV - 1][set]);
-            Quad<R> sum;
-            static_for<0, LV>([&](auto pi) {
-                constexpr int p = decltype(pi)::value;
-                const Quad<R> c = get<PLANE>(lds + FROM * 16 + ((tab[p] & 0xffffu) + child[p]), R());
-                const Quad<R> v = get<PLANE>(lds + L::kRec * 16 + ((tab[p] >> 16) + block[p]), R());
-                vertex<ROW, p == 0>(v, c, sum);
-            });
-            o = propagated<ROW>(P, sum);
-        }
-        put<PLANE>(lds + (TO + (set << LV)) * 16 + e * 16u, o);
+        Quad<R> sum[2];
+        vertices<R, LV, ROW, 2, PLANE>(lds_all, row4(tabs->lev[LV - 2][r], lane), sum);
+        char *to = lds + (TO + (set << LV) + s % H) * 16;
+#pragma unroll
+        for (int o = 0; o < 2; ++o) put<PLANE>(to + o * H * 16, propagated<ROW>(P, sum[o]));
     }
 }
 
-// Table entries of one chunk, loaded a chunk before their use.
+// Table words of a chunk, loaded a chunk before their use.
 template <int N, int W>
-struct ChunkTab {
-    using L = Split<N, W>;
-    u32x4 j[L::kChunkJ / L::S], w[L::kChunkW / L::S];
-    uint32_t con[L::C];
+struct ChunkRows {
+    u32x4 build[Split<N, W>::kRounds], con;
 };
 
 template <int N, int W>
-__device__ __forceinline__ ChunkTab<N, W> load_chunk_tab(int s, int chunk)
+__device__ __forceinline__ ChunkRows<N, W> load_chunk(int lane, int chunk)
 {
     using L = Split<N, W>;
-    static_assert(L::kChunkJ % L::S == 0 && L::kChunkW % L::S == 0, "a chunk fills whole rounds");
     const TabPtr<N, W> t = fresh_tables<N, W>();
-    ChunkTab<N, W> c;
+    ChunkRows<N, W> c;
 #pragma unroll
-    for (int r = 0; r < L::kChunkJ / L::S; ++r) c.j[r] = row4(t->mj[chunk * L::C + ((r * L::S + s) >> L::K)]);
-#pragma unroll
-    for (int r = 0; r < L::kChunkW / L::S; ++r) c.w[r] = row4(t->mw[chunk * L::C + ((r * L::S + s) >> L::U)]);
-#pragma unroll
-    for (int i = 0; i < L::C; ++i) c.con[i] = t->con[chunk * L::C + i][s];
+    for (int r = 0; r < L::kRounds; ++r) c.build[r] = row4(t->build[chunk][r], lane);
+    c.con = row4(t->con[chunk], lane);
     return c;
 }
 
-// The values of J (or W, ROW) of one chunk of sets to `to`.
-template <typename R, int N, int W, bool ROW, int PLANE>
-__device__ __forceinline__ void build_chunk(char *lds, int s, int chunk, const ChunkTab<N, W> &ct, char *to)
+// The values of J and W of chunk CH to its wave's buffer.  In a mixed round every
+// lane forms a column: a row's vertex blocks come with their halves swapped, and
+// its propagator is unity.
+template <typename R, int N, int W, int CH, int PLANE>
+__device__ __forceinline__ void build_chunk(char *lds_all, char *lds, int s, const ChunkRows<N, W> &rows)
 {
     using L = Split<N, W>;
-    constexpr int S = L::S, LV = ROW ? L::U : L::K, H = 1 << LV;
-    constexpr int FROM = ROW ? L::kR : L::kJ;
-    const uint32_t e = static_cast<uint32_t>(s) & (H - 1);
+    char *buf = lds + (L::kT + CH % W * L::kChunk) * 16;
+    static_for<0, L::kRounds>([&](auto ri) {
+        constexpr int r = decltype(ri)::value;
+        constexpr bool kRow = !L::kMixed && r * L::S >= L::kTasksJ;
+        constexpr int LV = kRow ? L::U : L::K, OUT = kRow ? L::kOutW : L::kOutJ, H = (1 << LV) / OUT;
+        Quad<R> sum[OUT];
+        vertices<R, LV, kRow, OUT, PLANE>(lds_all, rows.build[r], sum);
+        constexpr int kFirst = kRow ? r * L::S - L::kTasksJ : r * L::S;
+        const int in = (kFirst + s) / H;
+        if constexpr (!kRow) {
+            int at = (L::kProp + CH * L::C) + in;
+            if constexpr (L::kMixed) at = s < L::kTasksJ ? at : L::kOne;
+            const Quad<R> P = get<PLANE>(lds + at * 16, R());
 #pragma unroll
-    for (int r = 0; r < (L::C << LV) / S; ++r) {
-        const u32x4 tab = ROW ? ct.w[r] : ct.j[r];
-        Quad<R> sum;
-        static_for<0, LV>([&](auto pi) {
-            constexpr int p = decltype(pi)::value;
-            const Quad<R> c = get<PLANE>(lds + FROM * 16 + ((tab[p] & 0xffffu) + drop_bit(e, p) * 16u), R());
-            const Quad<R> v = get<PLANE>(lds + L::kRec * 16 + ((tab[p] >> 16) + (e >> p & 1u) * 16u), R());
-            vertex<ROW, p == 0>(v, c, sum);
-        });
-        if constexpr (!ROW) {
-            const int slot = chunk * L::C + ((r * S + s) >> LV);
-            // padding slots repeat the last set
-            const int at = L::kSlots > L::kSets ? (slot < L::kSets ? slot : L::kSets - 1) : slot;
-            sum = propagated<false>(get<PLANE>(lds + (L::kProp + at) * 16, R()), sum);
+            for (int o = 0; o < OUT; ++o) sum[o] = propagated<false>(P, sum[o]);
         }
-        put<PLANE>(to + (r * S + s) * 16, sum);
-    }
+        // W follows J in the buffer: a mixed round's sets are numbered on
+        static_assert(L::kChunkJ == L::C << L::K);
+        char *to = buf + ((kRow ? L::kChunkJ : 0) + (in << LV) + s % H) * 16;
+#pragma unroll
+        for (int o = 0; o < OUT; ++o) put<PLANE>(to + o * H * 16, sum[o]);
+    });
 }
 
-// Add the contraction W(B) . J(A) of walking slot SLOT (place I of the chunk
-// in `buf`) for the lane's four configurations: configuration bit 0 is photon
-// 0, bit 1 photon 1, and a set that holds a photon sees its bit lowest.
-template <typename R, int N, int W, int SLOT, int PLANE>
-__device__ __forceinline__ void contract(const char *buf, uint32_t con, double (&re)[4], double (&im)[4])
+// Add the contraction W(B) . J(A) of one set for the lane's four
+// configurations: configuration bit 0 is photon 0, bit 1 photon 1, and a set
+// that holds a photon sees its bit lowest.  kHeld: of photons 0 and 1, those in
+// A; `con`: the lane's places in the chunk buffer.
+template <typename R, uint32_t kHeld, int PLANE>
+__device__ __forceinline__ void contract(const char *lds_all, uint32_t con, double (&re)[4], double (&im)[4])
 {
-    using L = Split<N, W>;
-    constexpr int I = SLOT % L::C;
-    constexpr uint32_t kHeld = walk_set<N>(SLOT) & 3u;  // of photons 0 and 1, those in A
-    const char *jb = buf + I * (16 << L::K) + (con & 0xffffu);
-    const char *wb = buf + L::kChunkJ * 16 + I * (16 << L::U) + (con >> 16);
+    const char *jb = lds_all + (con & 0xffffu), *wb = lds_all + (con >> 16);
     constexpr int nj = kHeld == 3u ? 4 : kHeld == 0u ? 1 : 2, nw = 4 / nj;
     Quad<R> jv[nj], wv[nw];
 #pragma unroll
@@ -560,7 +608,7 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
     constexpr int PLANE = L::kEntries * P * 16;
     __shared__ __align__(16) char lds_all[(kF32 ? 1 : 2) * PLANE];
     const int lane = threadIdx.x & 63;
-    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int s = lane % S, pt = lane / S;
     char *lds = lds_all + pt * (L::kEntries * 16);
     const int64_t npts = d_count ? *d_count : count;
@@ -583,9 +631,21 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         const int64_t ic = i < npts ? i : npts - 1;
         return index ? static_cast<uint32_t>(index[ic]) : static_cast<uint32_t>(ic);
     };
-    LaneLoad q = load_lane(mom, ld, column(item), photon);
-    uint32_t src_next = column(item + stride);
+    // A point's inputs are loaded an item ahead (their columns two) at two waves
+    // per SIMD, and at its start (the column one ahead) at four, where the
+    // registers are short and the other waves cover the latency.
+    constexpr bool kAhead = WPE < 4;
+    LaneLoad q;
+    uint32_t src_next = column(item);
+    if constexpr (kAhead) {
+        q = load_lane(mom, ld, src_next, photon);
+        src_next = column(item + stride);
+    }
     for (;;) {
+        if constexpr (!kAhead) {
+            q = load_lane(mom, ld, src_next, photon);
+            src_next = column(item + stride);
+        }
         // ---- phase 1: FP64 set-up (as me2_compute's), one photon per lane
         bool ok = q.x1 == 0.0 && q.y1 == 0.0 && q.z1 > 0.0 && q.x2 == 0.0 && q.y2 == 0.0 && q.z2 < 0.0;
         int m = 0;
@@ -628,99 +688,92 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         const bool all_ok = (votes & group) == group;
         // the next item's inputs, loaded behind the walk (past the last item:
         // the last point again, never used)
-        const LaneLoad nxt = load_lane(mom, ld, src_next, photon);
-        const uint32_t src_after = column(item + 2 * stride);
-        phase_end<W>();
+        LaneLoad nxt;
+        uint32_t src_after = 0;
+        if constexpr (kAhead) {
+            nxt = load_lane(mom, ld, src_next, photon);
+            src_after = column(item + 2 * stride);
+        }
+        __syncthreads();
 
         // ---- phase 2 (two waves take the rounds of each end in turn)
         constexpr int kPj = L::props_j(), kPr = L::props_r();
         const int first = wave, other = W - 1 - wave;
         propagators<R, N, W, 0, kPj, L::kProp, PLANE>(lds, s, first, q0p, q0m, R(1));
         propagators<R, N, W, kPj, kPr, L::kT2, PLANE>(lds, s, other, p1p, p1m, R(-1));
-        phase_end<W>();
+        __syncthreads();
 
         // ---- phase 3
-        static_for<1, L::K>([&](auto li) {
-            build_level<R, N, W, decltype(li)::value, false, PLANE>(lds, s, first);
-            phase_end<W>();
+        build_first<R, N, W, false, PLANE>(lds, s, first);
+        __syncthreads();
+        static_for<2, L::K>([&](auto li) {
+            build_level<R, N, W, decltype(li)::value, false, PLANE>(lds_all, lds, lane, first);
+            __syncthreads();
         });
-        static_for<1, L::U>([&](auto li) {
-            build_level<R, N, W, decltype(li)::value, true, PLANE>(lds, s, other);
-            phase_end<W>();
+        build_first<R, N, W, true, PLANE>(lds, s, other);
+        __syncthreads();
+        static_for<2, L::U>([&](auto li) {
+            build_level<R, N, W, decltype(li)::value, true, PLANE>(lds_all, lds, lane, other);
+            __syncthreads();
         });
 
         // ---- phase 4
         propagators<R, N, W, kPj + kPr, L::kSets, L::kProp, PLANE>(lds, s, first, q0p, q0m, R(1));
-        phase_end<W>();
-
-        // ---- phase 5
-        double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
-        if constexpr (W == 1) {
-            ChunkTab<N, W> ct = load_chunk_tab<N, W>(s, 0), ct_next = load_chunk_tab<N, W>(s, 1);
-            build_chunk<R, N, W, false, PLANE>(lds, s, 0, ct, lds + L::kT * 16);
-            build_chunk<R, N, W, true, PLANE>(lds, s, 0, ct, lds + (L::kT + L::kChunkJ) * 16);
-            wave_phase_end();
-            static_for<0, L::kChunks>([&](auto ci) {
-                constexpr int c = decltype(ci)::value;
-                ChunkTab<N, W> ct_after = ct_next;
-                if constexpr (c + 2 < L::kChunks) ct_after = load_chunk_tab<N, W>(s, c + 2);
-                if constexpr (c + 1 < L::kChunks) {
-                    char *to = lds + (c % 2 == 0 ? L::kT2 : L::kT) * 16;
-                    build_chunk<R, N, W, false, PLANE>(lds, s, c + 1, ct_next, to);
-                    build_chunk<R, N, W, true, PLANE>(lds, s, c + 1, ct_next, to + L::kChunkJ * 16);
+        if constexpr (L::kMixed)
+            if (wave == W - 1 && s <= 2 * N) {
+                Quad<R> v = {R(1), R(1), R(0), R(0)};
+                if (s < 2 * N) {
+                    const Quad<R> u = get<PLANE>(lds + (L::kRec + L::kRecSize * (s >> 1) + (s & 1)) * 16, R());
+                    v = {u.c, u.d, u.a, u.b};
                 }
-                const char *buf = lds + (c % 2 == 0 ? L::kT : L::kT2) * 16;
+                put<PLANE>(lds + (L::kSwap + s) * 16, v);
+            }
+        __syncthreads();
+
+        // ---- phase 5: each wave takes every W-th chunk, through a buffer of its own
+        double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
+        auto walk = [&](auto wi) {
+            constexpr int w = decltype(wi)::value;
+            ChunkRows<N, W> rows = load_chunk<N, W>(lane, w);
+            static_for<0, (L::kChunks - w + W - 1) / W>([&](auto ci) {
+                constexpr int c = w + W * decltype(ci)::value;
+                ChunkRows<N, W> next = rows;
+                if constexpr (c + W < L::kChunks) next = load_chunk<N, W>(lane, c + W);
+                build_chunk<R, N, W, c, PLANE>(lds_all, lds, s, rows);
+                wave_phase_end();
                 static_for<0, L::C>([&](auto ii) {
                     constexpr int slot = c * L::C + decltype(ii)::value;
-                    if constexpr (slot < L::kSets) contract<R, N, W, slot, PLANE>(buf, ct.con[decltype(ii)::value], re, im);
+                    if constexpr (slot < L::kSets)
+                        contract<R, L::held(slot), PLANE>(lds_all, rows.con[decltype(ii)::value], re, im);
                 });
-                ct = ct_next;
-                ct_next = ct_after;
+                rows = next;
                 wave_phase_end();
             });
-        } else {
-            // each wave takes every other chunk, through a buffer of its own
-            auto walk = [&](auto wi) {
-                constexpr int w = decltype(wi)::value;
-                constexpr int kMine = (L::kChunks - w + W - 1) / W;
-                char *buf = lds + (w == 0 ? L::kT : L::kT2) * 16;
-                ChunkTab<N, W> ct = load_chunk_tab<N, W>(s, w);
-                static_for<0, kMine>([&](auto ci) {
-                    constexpr int c = w + W * decltype(ci)::value;
-                    ChunkTab<N, W> next = ct;
-                    if constexpr (c + W < L::kChunks) next = load_chunk_tab<N, W>(s, c + W);
-                    build_chunk<R, N, W, false, PLANE>(lds, s, c, ct, buf);
-                    build_chunk<R, N, W, true, PLANE>(lds, s, c, ct, buf + L::kChunkJ * 16);
-                    wave_phase_end();
-                    static_for<0, L::C>([&](auto ii) {
-                        constexpr int slot = c * L::C + decltype(ii)::value;
-                        if constexpr (slot < L::kSets) contract<R, N, W, slot, PLANE>(buf, ct.con[decltype(ii)::value], re, im);
-                    });
-                    ct = next;
-                    wave_phase_end();
-                });
-            };
-            if (wave == 0)
-                walk(std::integral_constant<int, 0>{});
-            else
-                walk(std::integral_constant<int, 1>{});
-            __syncthreads();
-            double *share = reinterpret_cast<double *>(lds_all) + lane;
-            if (wave == 1) {
+        };
+        static_assert(W == 2);
+        if (wave == 0)
+            walk(std::integral_constant<int, 0>{});
+        else
+            walk(std::integral_constant<int, 1>{});
+        __syncthreads();
+        static_assert((W - 1) * 8 * 64 * sizeof(double) <= sizeof(lds_all));
+        double *share = reinterpret_cast<double *>(lds_all) + lane;
+        if (wave > 0) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                share[(wave - 1) * 512 + (2 * h) * 64] = re[h];
+                share[(wave - 1) * 512 + (2 * h + 1) * 64] = im[h];
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int w = 0; w < W - 1; ++w)
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
-                    share[(2 * h) * 64] = re[h];
-                    share[(2 * h + 1) * 64] = im[h];
+                    re[h] += share[w * 512 + (2 * h) * 64];
+                    im[h] += share[w * 512 + (2 * h + 1) * 64];
                 }
-            }
-            __syncthreads();
-            if (wave == 0) {
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    re[h] += share[(2 * h) * 64];
-                    im[h] += share[(2 * h + 1) * 64];
-                }
-            }
         }
         double total = 0.0;
 #pragma unroll
@@ -735,9 +788,11 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         }
         item += stride;
         if (item >= end) break;
-        q = nxt;
-        src_next = src_after;
-        phase_end<W>();
+        if constexpr (kAhead) {
+            q = nxt;
+            src_next = src_after;
+        }
+        __syncthreads();
     }
 }
 
