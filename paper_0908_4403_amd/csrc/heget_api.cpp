@@ -688,6 +688,7 @@ struct McBufs {
     int64_t *d_count;
     int nchunks;
     bool apart;     // the weighted sums follow the amplitude pass (sums_apart)
+    bool beam;      // mom in the rows of GenParams::beam: nothing but the amplitude pass reads it
 };
 
 // Status of a finished Monte-Carlo call from its device flags.
@@ -731,6 +732,7 @@ heget_status enqueue_generation(int n, const heget_config &c, const McBufs &b, h
     gp.bins = bins;
     gp.bin_words = bin_words;
     gp.hel_out = b.hel;
+    gp.beam = b.beam;
     HG_HIP(heget::launch_gen(n, gp, b.mom, np, b.wfac, b.flag, b.bcount, s));
     HG_HIP(heget::launch_compact(b.bcount, b.flag, np, b.index, b.d_count, s));
     return HEGET_OK;
@@ -765,7 +767,7 @@ heget::Me2Args mc_me2_args(int n, const heget_config &c, const McBufs &b, unsign
     const bool epi = !b.apart;
     return heget::Me2Args{b.mom,      c.npoints,  b.index,  b.hel,  b.d_count,
                           c.npoints,  b.nchunks,  coef,     b.part, c.npoints,
-                          b.wfac,     epi ? b.partials : nullptr, epi ? b.wout : nullptr, flags};
+                          b.wfac,     epi ? b.partials : nullptr, epi ? b.wout : nullptr, flags, b.beam};
 }
 
 // A weighted histogram to fill beside the cross section (heget_xsec_hist).
@@ -826,6 +828,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     b.nchunks = sampled ? 1 : plan_chunks(*v, np / 2);
     b.apart = sums_apart(*v, b.nchunks);
     const bool fused = runs_fused(n, *cfg);
+    b.beam = !fused && !hist && !ev && v->beam_func;
     const size_t keep = fused ? 0 : size_t(np);  // points whose data goes through memory
     unsigned *flags;
     HG_TRY(scratch_bind(s));
@@ -950,7 +953,9 @@ void carve_batch(Arena &ar, int ncfg, const int *n, const heget_config *cfgs, in
         b.wout = nullptr;
         b.d_count = ar.take<int64_t>(1);
         // the persistent kernel always writes |M|^2 per chunk
-        b.apart = schedule == 1 || sums_apart(*pick_variant(cfgs[s].prec, n[s], np / 2), b.nchunks);
+        const heget::Me2Variant &v = *pick_variant(cfgs[s].prec, n[s], np / 2);
+        b.apart = schedule == 1 || sums_apart(v, b.nchunks);
+        b.beam = schedule != 1 && v.beam_func;
         b.part = b.apart ? ar.take<double>(size_t(b.nchunks) * size_t(np)) : nullptr;
         b.partials = ar.take<double>(size_t(3) * size_t((np + 63) / 64 + 1));  // + spare tile slot
         b.res = ar.take<double>(4);
@@ -1131,6 +1136,7 @@ void carve_static(int n, const heget_config &c, const heget::Me2Variant &v, Aren
     b = McBufs{};
     b.nchunks = sampled ? 1 : plan_chunks(v, np / 2);
     b.apart = sums_apart(v, b.nchunks);
+    b.beam = v.beam_func != nullptr;
     *flags = ar.take<unsigned>(1);
     b.d_count = ar.take<int64_t>(1);
     b.res = ar.take<double>(8);

@@ -26,7 +26,8 @@ struct Me2Variant {
                 // 2-4: meet in the middle (2: momenta once per point, 3: per walk,
                 // 4: per walk with the held v-bar-end currents in LDS)
                 // kLanesPs: helicities over the lanes of a wave (me2_lanes.hpp)
-    const void *func;  // kernel symbol
+    const void *func;       // kernel symbol
+    const void *beam_func;  // the same for momenta in the rows of GenParams::beam, or nullptr
 };
 
 constexpr int kLanesPs = 5;
@@ -43,7 +44,7 @@ const Me2Variant *me2_sampled(int prec, int n);
 
 // Arguments of one amplitude launch.
 struct Me2Args {
-    const double *mom;       // SoA [(n+2)*4][ld]
+    const double *mom;       // SoA [(n+2)*4][ld], or the 1 + 4 n rows of GenParams::beam
     int64_t ld;
     const int32_t *index;    // survivor -> column of mom (and of wfac), or nullptr (identity)
     const uint16_t *hel;     // sampled helicity configuration per column (H = 0 shapes only)
@@ -57,6 +58,7 @@ struct Me2Args {
     double *partials;        // one chunk: per-tile weighted triples instead of out
     double *wout;            // with partials: also each point's weight, or nullptr
     unsigned *flags;         // bit 0 set if a result is not finite
+    bool beam;               // which of the two
 };
 
 hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream);

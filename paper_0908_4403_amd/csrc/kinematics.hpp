@@ -276,6 +276,7 @@ struct GenParams {
     uint16_t *hel_out;     // if set, the sampled helicity configuration of every point
     unsigned long long *bins;  // if set, bin_words words zeroed by the launch (a histogram's bins)
     int bin_words;
+    bool beam;             // momenta for the amplitude pass alone: one row, E, for the two beams (E, 0, 0, +-E)
 };
 
 // Helicity configuration drawn for `point` in sampling mode (the paper's

@@ -16,29 +16,35 @@
 
 namespace heget {
 
-// SoA rows of one point: quark momenta (E, 0, 0, +-E), then the photons.  The
-// row of the workgroup's first point is uniform (scalar address arithmetic), a
-// lane adds its place in the workgroup.
+// SoA rows of one point: quark momenta (E, 0, 0, +-E), then the photons; with
+// `beam` only E for the quarks: 21 rows instead of 28 at n = 5, for this kernel
+// and for the gathering reads of the next (hadronic n = 5 of 4.2e6 points 217 ->
+// 209 us here and 913 -> 885 in the amplitude kernel, which also needs fewer
+// registers; FP64 n = 4 of 1e6 points 45 -> 43 and 108 -> 106).  The row of the workgroup's first point is uniform (scalar
+// address arithmetic), a lane adds its place in the workgroup.
 template <int N>
-__device__ __forceinline__ void store_point(double *__restrict__ mom, int64_t ld, double e, const Vec4 (&k)[N])
+__device__ __forceinline__ void store_point(double *__restrict__ mom, int64_t ld, bool beam, double e,
+                                            const Vec4 (&k)[N])
 {
     double *block = mom + static_cast<int64_t>(blockIdx.x) * 256;
     const uint32_t t = threadIdx.x;
-    auto put = [&](int row, double v) { (block + row * ld)[t] = v; };
-    put(0, e);
-    put(1, 0.0);
-    put(2, 0.0);
-    put(3, e);
-    put(4, e);
-    put(5, 0.0);
-    put(6, 0.0);
-    put(7, -e);
+    block[t] = e;
+    if (!beam) {
+        const double rest[7] = {0.0, 0.0, e, e, 0.0, 0.0, -e};
+#pragma unroll
+        for (int r = 0; r < 7; ++r) {
+            block += ld;
+            block[t] = rest[r];
+        }
+    }
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        put(8 + 4 * j, k[j].e);
-        put(9 + 4 * j, k[j].x);
-        put(10 + 4 * j, k[j].y);
-        put(11 + 4 * j, k[j].z);
+        const double v[4] = {k[j].e, k[j].x, k[j].y, k[j].z};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            block += ld;
+            block[t] = v[c];
+        }
     }
 }
 
@@ -63,7 +69,7 @@ gen_kernel(GenParams g, double *__restrict__ mom, int64_t ld, double *__restrict
             Vec4 k[N];
             double e;
             s = point_setup_screened<N, MODE>(g, static_cast<uint64_t>(g.first + i), tab, k, e, w, y);
-            store_point<N>(mom, ld, e, k);
+            store_point<N>(mom, ld, g.beam, e, k);
         }
         if (s < 0) {
             // Rare: decide in FP64 from the momenta just stored.  The row
@@ -71,12 +77,12 @@ gen_kernel(GenParams g, double *__restrict__ mom, int64_t ld, double *__restrict
             // compiler reloads them instead of keeping every momentum live
             // through the whole kernel (which costs two waves per SIMD).
             __threadfence_block();  // this thread's stores above are visible to its loads
-            const double *m = mom + i;
+            const double *m = mom + (g.beam ? 1 : 8) * ld + i;
             asm volatile("" : "+v"(m));
             Vec4 k[N];
 #pragma unroll
             for (int j = 0; j < N; ++j)
-                k[j] = {m[(8 + 4 * j) * ld], m[(9 + 4 * j) * ld], m[(10 + 4 * j) * ld], m[(11 + 4 * j) * ld]};
+                k[j] = {m[4 * j * ld], m[(4 * j + 1) * ld], m[(4 * j + 2) * ld], m[(4 * j + 3) * ld]};
             s = pass_cuts_fp64<N>(k, y, g.pt_min, g.eta_max, g.dr_min) ? 1 : 0;
         }
         acc = s == 1;

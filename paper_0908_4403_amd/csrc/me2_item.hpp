@@ -14,11 +14,16 @@
 namespace heget {
 
 // Inputs of one point of a work item, loaded ahead of the walk that uses them.
-template <int N>
+// BEAM: the momenta as the Monte-Carlo path keeps them between its kernels, the
+// beams (E, 0, 0, +-E) by their one energy.
+template <bool BEAM>
+constexpr int kBeamRows = BEAM ? 1 : 8;
+
+template <int N, bool BEAM = false>
 struct PointLoad {
-    double x[8 + 4 * N];  // momenta p1, p2, k1..kN
-    double wf;            // weight factor (0 without one)
-    uint32_t hel;         // sampled helicity configuration (0 without one)
+    double x[kBeamRows<BEAM> + 4 * N];  // momenta p1, p2 (or E), k1..kN
+    double wf;                          // weight factor (0 without one)
+    uint32_t hel;                       // sampled helicity configuration (0 without one)
 };
 
 // Column of mom holding lane `lane` of `tile`: past the last point the tile
@@ -32,14 +37,14 @@ __device__ __forceinline__ uint32_t point_column(const int32_t *__restrict__ ind
     return index ? static_cast<uint32_t>(index[ic]) : static_cast<uint32_t>(ic);
 }
 
-template <int N>
-__device__ __forceinline__ PointLoad<N> load_point(const double *__restrict__ mom, int64_t ld,
+template <int N, bool BEAM = false>
+__device__ __forceinline__ PointLoad<N, BEAM> load_point(const double *__restrict__ mom, int64_t ld,
                                                    uint32_t src, const double *__restrict__ wfac,
                                                    const uint16_t *__restrict__ hel)
 {
-    PointLoad<N> q;
+    PointLoad<N, BEAM> q;
 #pragma unroll
-    for (int r = 0; r < 8 + 4 * N; ++r) q.x[r] = mom[r * ld + src];
+    for (int r = 0; r < kBeamRows<BEAM> + 4 * N; ++r) q.x[r] = mom[r * ld + src];
     q.wf = wfac ? wfac[src] : 0.0;
     q.hel = hel ? static_cast<uint32_t>(hel[src]) : 0u;
     return q;
@@ -50,15 +55,18 @@ __device__ __forceinline__ PointLoad<N> load_point(const double *__restrict__ mo
 // of R).  H = 0 selects helicity sampling: one walk per lane with the
 // configuration q.hel (bit j set = photon j has helicity +1) instead of the
 // sum.  NaN where the preconditions do not hold.
-template <typename R, int N, int MB, int H, int CL, int PS = 0>
-__device__ __forceinline__ double me2_value(const PointLoad<N> &q, int chunk, int nchunks, double coef, R *tab,
+template <typename R, int N, int MB, int H, int CL, int PS = 0, bool BEAM = false>
+__device__ __forceinline__ double me2_value(const PointLoad<N, BEAM> &q, int chunk, int nchunks, double coef, R *tab,
                                             int lane)
 {
     constexpr bool kTopInLds = N > MB;
 
     // ---- FP64 set-up: preconditions, power-of-two scale, light-cone photons
-    const double E1 = q.x[0], p1x = q.x[1], p1y = q.x[2], p1z = q.x[3];
-    const double E2 = q.x[4], p2x = q.x[5], p2y = q.x[6], p2z = q.x[7];
+    double E1 = q.x[0], p1x = 0.0, p1y = 0.0, p1z = E1, E2 = E1, p2x = 0.0, p2y = 0.0, p2z = -E1;
+    if constexpr (!BEAM) {
+        p1x = q.x[1], p1y = q.x[2], p1z = q.x[3];
+        E2 = q.x[4], p2x = q.x[5], p2y = q.x[6], p2z = q.x[7];
+    }
     bool ok = p1x == 0.0 && p1y == 0.0 && p1z > 0.0 && p2x == 0.0 && p2y == 0.0 && p2z < 0.0;
     int m = 0;
     frexp(E1 + E2, &m);
@@ -72,7 +80,7 @@ __device__ __forceinline__ double me2_value(const PointLoad<N> &q, int chunk, in
     double norm_den = 1.0;  // product of the photons' 2 E^2 / pT^2, divided out once
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        const int r = 8 + 4 * j;
+        const int r = kBeamRows<BEAM> + 4 * j;
         const double E = q.x[r] * sc, kx = q.x[r + 1] * sc, ky = q.x[r + 2] * sc, kz = q.x[r + 3] * sc;
         const double pt2 = kx * kx + ky * ky;
         ok = ok && E > 0.0 && pt2 > 0.0;
@@ -128,8 +136,8 @@ __device__ __forceinline__ double me2_value(const PointLoad<N> &q, int chunk, in
 // compensation, sum of squares) of |M|^2 * wf (the Monte-Carlo weights of
 // eq. (1)-(2)), and the weight itself at wout[i] when wout is set; otherwise
 // |M|^2 of the chunk at out[chunk * ld_out + i].
-template <typename R, int N, int MB, int H, int CL, bool kWeighted = true, int PS = 0>
-__device__ __forceinline__ void me2_compute(const PointLoad<N> &q, int64_t npts, int64_t tile,
+template <typename R, int N, int MB, int H, int CL, bool kWeighted = true, int PS = 0, bool BEAM = false>
+__device__ __forceinline__ void me2_compute(const PointLoad<N, BEAM> &q, int64_t npts, int64_t tile,
                                             int chunk, int nchunks, double coef,
                                             double *__restrict__ out, int64_t ld_out,
                                             double *__restrict__ partials, double *__restrict__ wout,
@@ -182,7 +190,7 @@ __device__ __forceinline__ void me2_item(const double *__restrict__ mom, int64_t
 // photon table), for more instruction-level parallelism per wave; the
 // weighted partial-sum buffer needs one spare tile slot after the last tile.
 // PS = 1 walks the top levels by prefix sets (prefix_sets in me2_tree.hpp).
-template <typename R, int N, int MB, int H, int CL, int WPB, int PF, int WPE, int PPL, int PS>
+template <typename R, int N, int MB, int H, int CL, int WPB, int PF, int WPE, int PPL, int PS, bool BEAM>
 __global__ void __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
 me2_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict__ index,
            const uint16_t *__restrict__ hel, const int64_t *__restrict__ d_count, int64_t count,
@@ -225,7 +233,7 @@ me2_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict
         for (; item < end; item += stride) {
             const int64_t tile = tile_of(item);
             const int chunk = static_cast<int>(item - tile * nchunks);
-            const PointLoad<N> q = load_point<N>(mom, ld, point_column(index, npts, tile, lane), wf, hl);
+            const PointLoad<N, BEAM> q = load_point<N, BEAM>(mom, ld, point_column(index, npts, tile, lane), wf, hl);
             me2_compute<R, N, MB, H, CL, true, PS>(q, npts, tile, chunk, nchunks, coef, out, ld_out,
                                                    partials, wout, flags, tab, lane);
         }
@@ -233,10 +241,10 @@ me2_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict
         for (; item < end; item += stride) {
             const int64_t group = tile_of(item);
             const int chunk = static_cast<int>(item - group * nchunks);
-            PointLoad<N> q[PPL];
+            PointLoad<N, BEAM> q[PPL];
 #pragma unroll
             for (int p = 0; p < PPL; ++p)
-                q[p] = load_point<N>(mom, ld, point_column(index, npts, group * PPL + p, lane), wf, hl);
+                q[p] = load_point<N, BEAM>(mom, ld, point_column(index, npts, group * PPL + p, lane), wf, hl);
             // unconditional, so that the walks can share one basic block: a
             // tile past the last one (only in the last group) holds no valid
             // point, stores nothing and writes a zero tile sum into the
@@ -256,10 +264,10 @@ me2_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict
             const int64_t t = tile_of(it);
             return t < last_tile ? t : last_tile;
         };
-        PointLoad<N> cur = load_point<N>(mom, ld, point_column(index, npts, tile_of(item), lane), wf, hl);
+        PointLoad<N, BEAM> cur = load_point<N, BEAM>(mom, ld, point_column(index, npts, tile_of(item), lane), wf, hl);
         uint32_t src_next = point_column(index, npts, ahead(item + stride), lane);
         for (;;) {
-            const PointLoad<N> nxt = load_point<N>(mom, ld, src_next, wf, hl);
+            const PointLoad<N, BEAM> nxt = load_point<N, BEAM>(mom, ld, src_next, wf, hl);
             const uint32_t src_after = point_column(index, npts, ahead(item + 2 * stride), lane);
             const int64_t tile = tile_of(item);
             const int chunk = static_cast<int>(item - tile * nchunks);
@@ -278,7 +286,18 @@ template <typename R, int N, int MB, int H, int CL, int WPB, int PF = 0, int WPE
 constexpr Me2Variant variant()
 {
     return Me2Variant{std::is_same<R, float>::value ? 1 : 0, N, MB, H, CL, WPB, PF, WPE, PPL, PS,
-                      reinterpret_cast<const void *>(&me2_kernel<R, N, MB, H, CL, WPB, PF, WPE, PPL, PS>)};
+                      reinterpret_cast<const void *>(&me2_kernel<R, N, MB, H, CL, WPB, PF, WPE, PPL, PS, false>),
+                      nullptr};
+}
+
+// A variant with a twin that reads the Monte-Carlo path's own momenta (BEAM).
+template <typename R, int N, int MB, int H, int CL, int WPB, int PF = 0, int WPE = 0, int PPL = 1,
+          int PS = 0>
+constexpr Me2Variant mc_variant()
+{
+    Me2Variant v = variant<R, N, MB, H, CL, WPB, PF, WPE, PPL, PS>();
+    v.beam_func = reinterpret_cast<const void *>(&me2_kernel<R, N, MB, H, CL, WPB, PF, WPE, PPL, PS, true>);
+    return v;
 }
 
 }  // namespace heget

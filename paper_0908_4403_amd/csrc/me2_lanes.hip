@@ -8,7 +8,8 @@ template <typename R, int N, int W, int WPE>
 constexpr Me2Variant lanes_variant()
 {
     return Me2Variant{std::is_same<R, float>::value ? 1 : 0, N, N, 1 << N, 2, W, 1, WPE, 1, kLanesPs,
-                      reinterpret_cast<const void *>(&lanes::me2_lanes_kernel<R, N, W, WPE>)};
+                      reinterpret_cast<const void *>(&lanes::me2_lanes_kernel<R, N, W, WPE, false>),
+                      reinterpret_cast<const void *>(&lanes::me2_lanes_kernel<R, N, W, WPE, true>)};
 }
 
 // (waves on a wave's points, waves per SIMD): see me2_lanes.hpp

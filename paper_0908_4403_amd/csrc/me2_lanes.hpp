@@ -58,6 +58,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "me2_item.hpp"
 #include "me2_tree.hpp"
 #include "reduce.hpp"
 
@@ -583,19 +584,23 @@ struct LaneLoad {
     double e1, x1, y1, z1, e2, x2, y2, z2, e, x, y, z;
 };
 
+template <bool BEAM>
 __device__ __forceinline__ LaneLoad load_lane(const double *__restrict__ mom, int64_t ld, uint32_t src,
                                               int photon)
 {
-    const double *k = mom + (8 + 4 * photon) * ld + src;
+    const double *k = mom + (kBeamRows<BEAM> + 4 * photon) * ld + src;
     const double *b = mom + src;
-    return {b[0], b[ld], b[2 * ld], b[3 * ld], b[4 * ld], b[5 * ld], b[6 * ld], b[7 * ld],
-            k[0], k[ld], k[2 * ld], k[3 * ld]};
+    if constexpr (BEAM)
+        return {b[0], 0.0, 0.0, b[0], b[0], 0.0, 0.0, -b[0], k[0], k[ld], k[2 * ld], k[3 * ld]};
+    else
+        return {b[0], b[ld], b[2 * ld], b[3 * ld], b[4 * ld], b[5 * ld], b[6 * ld], b[7 * ld],
+                k[0], k[ld], k[2 * ld], k[3 * ld]};
 }
 
 // Work item: P consecutive points of the list.  Resident waves, each walking
 // its items in turn and loading the next item's inputs ahead; |M|^2 of point
 // i at out[i].  Arguments as me2_kernel's (one chunk, no weighted epilogue).
-template <typename R, int N, int W, int WPE>
+template <typename R, int N, int W, int WPE, bool BEAM>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE)))
 me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict__ index,
                  const uint16_t *__restrict__, const int64_t *__restrict__ d_count, int64_t count, int,
@@ -638,12 +643,12 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
     LaneLoad q;
     uint32_t src_next = column(item);
     if constexpr (kAhead) {
-        q = load_lane(mom, ld, src_next, photon);
+        q = load_lane<BEAM>(mom, ld, src_next, photon);
         src_next = column(item + stride);
     }
     for (;;) {
         if constexpr (!kAhead) {
-            q = load_lane(mom, ld, src_next, photon);
+            q = load_lane<BEAM>(mom, ld, src_next, photon);
             src_next = column(item + stride);
         }
         // ---- phase 1: FP64 set-up (as me2_compute's), one photon per lane
@@ -691,7 +696,7 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         LaneLoad nxt;
         uint32_t src_after = 0;
         if constexpr (kAhead) {
-            nxt = load_lane(mom, ld, src_next, photon);
+            nxt = load_lane<BEAM>(mom, ld, src_next, photon);
             src_after = column(item + 2 * stride);
         }
         __syncthreads();

@@ -73,26 +73,28 @@ const Me2Variant *me2_sampled(int prec, int n)
 }
 
 // Blocks of a kernel that fit on the device at once (resident), per kernel.
-static int64_t resident_blocks(const Me2Variant &v)
+static int64_t resident_blocks(const void *func, int wpb)
 {
     static std::mutex mu;
     static std::map<const void *, int64_t> cache;
     std::lock_guard<std::mutex> lk(mu);
-    auto it = cache.find(v.func);
+    auto it = cache.find(func);
     if (it != cache.end()) return it->second;
     int dev = 0, per_cu = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, v.func, v.wpb * 64, 0) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, func, wpb * 64, 0) != hipSuccess ||
         per_cu <= 0 || cus <= 0)
         return 0;  // unknown: one wave per item
     const int64_t r = static_cast<int64_t>(per_cu) * cus;
-    cache[v.func] = r;
+    cache[func] = r;
     return r;
 }
 
 hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream)
 {
+    const void *func = a.beam ? v.beam_func : v.func;
+    if (!func) return hipErrorInvalidValue;
     const int64_t ntiles = (a.count + 63) / 64;
     int64_t items = (ntiles + v.ppl - 1) / v.ppl * a.nchunks;
     if (v.ps == kLanesPs) {  // a workgroup's wave(s) share 2^(8 - n) points, |M|^2 of each to out
@@ -103,7 +105,7 @@ hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream)
     if (items == 0) return hipSuccess;
     int64_t blocks = v.ps == kLanesPs ? items : (items + v.wpb - 1) / v.wpb;
     if (v.pf) {
-        const int64_t r = resident_blocks(v);
+        const int64_t r = resident_blocks(func, v.wpb);
         if (r > 0 && r < blocks) blocks = r;
     }
     void *args[] = {const_cast<double **>(&a.mom), const_cast<int64_t *>(&a.ld),
@@ -113,7 +115,7 @@ hipError_t launch_me2(const Me2Variant &v, const Me2Args &a, hipStream_t stream)
                     const_cast<double **>(&a.out), const_cast<int64_t *>(&a.ld_out),
                     const_cast<double **>(&a.wfac), const_cast<double **>(&a.partials),
                     const_cast<double **>(&a.wout), const_cast<unsigned **>(&a.flags)};
-    return hipLaunchKernel(v.func, dim3(static_cast<unsigned>(blocks)), dim3(v.wpb * 64), args, 0,
+    return hipLaunchKernel(func, dim3(static_cast<unsigned>(blocks)), dim3(v.wpb * 64), args, 0,
                            stream);
 }
 

@@ -14,7 +14,7 @@
 namespace heget {
 
 extern const Me2Variant kShapesWhole[] = {
-    variant<float, 5, 5, 32, 2, 1, 0, 0, 1, 2>(),
+    mc_variant<float, 5, 5, 32, 2, 1, 0, 0, 1, 2>(),
 };
 extern const int kShapesWholeCount = sizeof(kShapesWhole) / sizeof(Me2Variant);
 
