@@ -306,7 +306,9 @@ heget_status heget_timing_read(double *me2_ms, int64_t *me2_launches, int reset)
  *                        per point -- the same meeting in the middle with the
  *                        helicities of a point spread over 2^(n-2) lanes of a
  *                        wave and every subset current formed once for the
- *                        helicities it depends on (helicities_per_walk = 2^n) */
+ *                        helicities it depends on (helicities_per_walk = 2^n);
+ *                        6 (n = 5; the default for large calls): as 5 over two
+ *                        lanes */
 typedef struct {
     int32_t unrolled, helicities_per_walk, closing, waves_per_block, prefetch, waves_per_simd,
         points_per_lane, prefix_sets;

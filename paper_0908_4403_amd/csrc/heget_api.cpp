@@ -324,11 +324,13 @@ const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, in
 // helicities to share the currents (points/s, walk against lanes, at 1, 517
 // and about 1e5 points alike: n = 6 FP32 3.3e8 against 7.6e8, FP64 9.7e7
 // against 4.8e8; n = 8 1.2e6 against 5.1e7 in FP64).
-// n = 5: a walk of all 32 configurations (FP32) or eight (FP64, the first
-// shape of the list); lanes would run at 1.07e9 and 5.6e8 points/s against
-// 2.7e9 and 1.1e9.  Below one wave per two SIMDs (kFillItems / 2 tiles) a walk
-// of fewer configurations that splits into chunks ends sooner: 500 points 14
-// instead of 23 us (FP32, eight), 14 instead of 18 us (FP64, four); at 20 000
+// n = 5: two lanes per point; lanes would run at 1.07e9 (FP32) and 5.6e8 (FP64)
+// points/s against 3.1e9 and 1.5e9.  FP32 calls that leave it without a second
+// wave per SIMD (up to kFillItems tiles) run a walk of all 32 configurations (65
+// 536 points 28.6 against 32.5 us; 100 000: 50.9 against 49.7).  Below one wave
+// per two SIMDs (kFillItems / 2 tiles) a walk of fewer configurations that splits
+// into chunks ends sooner: 500 points 14 instead of 23 us (FP32, eight, against
+// the walk of all), 14 instead of 18 us (FP64, four, against eight); at 20 000
 // points 19 against 25 us (FP32) and 36 against 37 us (FP64).
 // n <= 4: the first shape of the list.
 const heget::Me2Variant *default_variant(int prec, int n, int64_t points)
@@ -338,7 +340,8 @@ const heget::Me2Variant *default_variant(int prec, int n, int64_t points)
                                                           : find_variant(prec, 5, 5, 4, 2, 1, 0, 0, 1, 3);
         if (few) return few;
     }
-    const heget::Me2Variant *all = heget::me2_shared(prec, n);
+    const bool whole = n == 5 && prec == HEGET_FP32 && (points + 63) / 64 <= kFillItems;
+    const heget::Me2Variant *all = heget::me2_shared(prec, n, whole ? 1 : 0);
     return all ? all : heget::me2_default(prec, n);
 }
 
@@ -363,8 +366,9 @@ const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, in
     const heget::Me2Variant *v = heget::me2_variants(&cnt);
     for (int i = 0; i < cnt; ++i)
         if (is(v[i])) return &v[i];
-    const heget::Me2Variant *all = heget::me2_shared(prec, n);
-    return all && is(*all) ? all : nullptr;
+    for (int i = 0; const heget::Me2Variant *all = heget::me2_shared(prec, n, i); ++i)
+        if (is(*all)) return all;
+    return nullptr;
 }
 
 heget_shape shape_of(const heget::Me2Variant &v)
@@ -1689,12 +1693,14 @@ heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape
     HG_HIP(hipEventCreate(&e1));
     int cnt = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
-    const heget::Me2Variant *shared = heget::me2_shared(prec, n);
+    std::vector<const heget::Me2Variant *> tried;
+    for (int i = 0; const heget::Me2Variant *shared = heget::me2_shared(prec, n, i); ++i) tried.push_back(shared);
+    for (int i = 0; i < cnt; ++i)
+        if (all[i].prec == prec && all[i].n == n) tried.push_back(&all[i]);
     const heget::Me2Variant *best = nullptr;
     double best_ms = 0.0;
-    for (int i = shared ? -1 : 0; i < cnt; ++i) {
-        const heget::Me2Variant &v = i < 0 ? *shared : all[i];
-        if (v.prec != prec || v.n != n) continue;
+    for (const heget::Me2Variant *p : tried) {
+        const heget::Me2Variant &v = *p;
         const int nchunks = plan_chunks(v, npoints);
         double *out = nullptr;
         HG_TRY(scratch_t<double>(S_OUT, size_t(nchunks) * size_t(npoints), &out));
@@ -1755,7 +1761,8 @@ heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *s
     int cnt = 0, k = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
     const heget::Me2Variant *cur = pick_variant(prec, n, kMaxPoints);
-    if (cur == heget::me2_shared(prec, n)) cur = heget::me2_default(prec, n);  // not in the list
+    for (int i = 0; const heget::Me2Variant *all = heget::me2_shared(prec, n, i); ++i)
+        if (cur == all) cur = heget::me2_default(prec, n);  // not in the list
     if (cur) {  // the shape in use first
         if (k < max) shapes[k] = shape_of(*cur);
         ++k;

@@ -26,19 +26,21 @@ struct Me2Variant {
                 // 2-4: meet in the middle (2: momenta once per point, 3: per walk,
                 // 4: per walk with the held v-bar-end currents in LDS)
                 // kLanesPs: helicities over the lanes of a wave (me2_lanes.hpp)
+                // kPairPs: over two lanes (me2_pair.hpp)
     const void *func;       // kernel symbol
     const void *beam_func;  // the same for momenta in the rows of GenParams::beam, or nullptr
 };
 
 constexpr int kLanesPs = 5;
+constexpr int kPairPs = 6;
 
 // All compiled walk variants (one lane per point; static table) and the first one per (prec, n).
 const Me2Variant *me2_variants(int *count);
 const Me2Variant *me2_default(int prec, int n);
-// The kernel that forms every subset current once per point for (prec, n), outside the list of
-// walk variants, or nullptr: helicities over the lanes of a wave (me2_lanes.hpp) or, for the
-// float n = 5, one walk of all of them.
-const Me2Variant *me2_shared(int prec, int n);
+// The i-th kernel that forms every subset current once per point for (prec, n), outside the list
+// of walk variants, or nullptr: helicities over the lanes of a wave (n >= 6), over two lanes (n = 5)
+// or, for the float n = 5 the second one, one walk of all of them.
+const Me2Variant *me2_shared(int prec, int n, int i = 0);
 // The helicity-sampling kernel (h = 0) for (prec, n).
 const Me2Variant *me2_sampled(int prec, int n);
 

@@ -548,6 +548,22 @@ __device__ __forceinline__ void build_chunk(char *lds_all, char *lds, int s, con
     });
 }
 
+// Add w . g, in the working precision, to an FP64 sum.
+template <typename R>
+__device__ __forceinline__ void add_product(const Quad<R> &w, const Quad<R> &g, double &re, double &im)
+{
+    R ar = w.a * g.a;
+    ar = fma(-w.b, g.b, ar);
+    ar = fma(w.c, g.c, ar);
+    ar = fma(-w.d, g.d, ar);
+    R ai = w.a * g.b;
+    ai = fma(w.b, g.a, ai);
+    ai = fma(w.c, g.d, ai);
+    ai = fma(w.d, g.c, ai);
+    re += static_cast<double>(ar);
+    im += static_cast<double>(ai);
+}
+
 // Add the contraction W(B) . J(A) of one set for the lane's four
 // configurations: configuration bit 0 is photon 0, bit 1 photon 1, and a set
 // that holds a photon sees its bit lowest.  kHeld: of photons 0 and 1, those in
@@ -566,16 +582,7 @@ __device__ __forceinline__ void contract(const char *lds_all, uint32_t con, doub
     for (int h = 0; h < 4; ++h) {
         const Quad<R> &g = jv[kHeld == 3u ? h : kHeld == 0u ? 0 : kHeld == 1u ? (h & 1) : (h >> 1)];
         const Quad<R> &w = wv[kHeld == 3u ? 0 : kHeld == 0u ? h : kHeld == 1u ? (h >> 1) : (h & 1)];
-        R ar = w.a * g.a;
-        ar = fma(-w.b, g.b, ar);
-        ar = fma(w.c, g.c, ar);
-        ar = fma(-w.d, g.d, ar);
-        R ai = w.a * g.b;
-        ai = fma(w.b, g.a, ai);
-        ai = fma(w.c, g.d, ai);
-        ai = fma(w.d, g.c, ai);
-        re[h] += static_cast<double>(ar);
-        im[h] += static_cast<double>(ai);
+        add_product(w, g, re[h], im[h]);
     }
 }
 

@@ -20,6 +20,8 @@ extern const Me2Variant kShapesSampled[], kShapesSampledMeet8[];
 extern const int kShapesSampledCount, kShapesSampledMeet8Count;
 extern const Me2Variant kShapesLanes[];
 extern const int kShapesLanesCount;
+extern const Me2Variant kShapesPair[];
+extern const int kShapesPairCount;
 extern const Me2Variant kShapesWhole[];
 extern const int kShapesWholeCount;
 
@@ -54,12 +56,13 @@ const Me2Variant *me2_default(int prec, int n)
     return nullptr;
 }
 
-const Me2Variant *me2_shared(int prec, int n)
+const Me2Variant *me2_shared(int prec, int n, int i)
 {
-    for (int i = 0; i < kShapesLanesCount; ++i)
-        if (kShapesLanes[i].prec == prec && kShapesLanes[i].n == n) return &kShapesLanes[i];
-    for (int i = 0; i < kShapesWholeCount; ++i)
-        if (kShapesWhole[i].prec == prec && kShapesWhole[i].n == n) return &kShapesWhole[i];
+    const Me2Variant *tabs[] = {kShapesLanes, kShapesPair, kShapesWhole};
+    const int counts[] = {kShapesLanesCount, kShapesPairCount, kShapesWholeCount};
+    for (int t = 0; t < 3; ++t)
+        for (int k = 0; k < counts[t]; ++k)
+            if (tabs[t][k].prec == prec && tabs[t][k].n == n && i-- == 0) return &tabs[t][k];
     return nullptr;
 }
 

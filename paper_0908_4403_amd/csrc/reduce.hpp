@@ -31,8 +31,8 @@ template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v)
 {
     const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b), CTRL, 0xF, 0xF, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b >> 32), CTRL, 0xF, 0xF, false);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp(static_cast<uint32_t>(b), CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp(static_cast<uint32_t>(b >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
