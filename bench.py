@@ -76,7 +76,10 @@ def run_steps(H, torch, n, cfg, steps, warmup, nstreams=1):
     host callback).  The step time is taken without per-kernel events (an
     event record stalls the stream by a few microseconds); the amplitude kernel
     is then timed over at least 200 further passes, on one stream, with HIP
-    events on the launch stream."""
+    events on the launch stream.  Where the step runs generation and amplitudes
+    as one kernel (n <= 4) these passes run them apart, which adds the weights
+    in another order: their results agree among themselves, and with the steps'
+    to the rounding of the sums."""
     kreps = max(steps, 200)
     total = warmup + steps + kreps
     buf = torch.zeros((total, 64), dtype=torch.uint8, device="cuda")
@@ -101,7 +104,10 @@ def run_steps(H, torch, n, cfg, steps, warmup, nstreams=1):
     H.timing_enable(False)
     host = buf.cpu().numpy()
     res = [H.result_from_bytes(host[k]) for k in range(total)]
-    assert all(r == res[0] for r in res), "steps disagree"
+    apart = res[warmup + steps:]
+    assert all(r == res[0] for r in res[:warmup + steps]) and all(r == apart[0] for r in apart), "steps disagree"
+    assert res[0]["n_acc"] == apart[0]["n_acc"] and abs(res[0]["sigma_fb"] / apart[0]["sigma_fb"] - 1) <= 1e-12, \
+        "timed kernel passes disagree with the steps"
     return (t1 - t0) * 1e3 / steps, me2_ms / max(launches, 1), launches, res[0]
 
 
@@ -139,11 +145,14 @@ def mixed_batch(H, torch, prec, steps):
 
 
 def kernel_name(prec, n, shape):
-    """The amplitude kernel of a shape (prefix_sets = 5: helicities over lanes) as profiles name it."""
+    """The amplitude kernel of a shape (prefix_sets = 5, 6: helicities over lanes, over two lanes) as
+    profiles name it, reading all momentum rows."""
     real = "float" if prec == "fp32" else "double"
     if shape[7] == 5:
-        return f"me2_lanes_kernel<{real},{n}>"
-    return "me2_kernel<{},{},{}>".format(real, n, ",".join(str(v) for v in shape))
+        return f"lanes::me2_lanes_kernel<{real},{n},{shape[3]},{shape[5]},false>"
+    if shape[7] == 6:
+        return f"pairs::me2_pair_kernel<{real},{n},{shape[5]},false>"
+    return "me2_kernel<{},{},{},false>".format(real, n, ",".join(str(v) for v in shape))
 
 
 def per_n(H, torch, tune, ns=range(2, 9)):
@@ -524,6 +533,7 @@ def main():
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
                      "kernel": kname,
                      "kernel_ms": k32,
+                     "kernel_timed": "in passes of their own that run it apart from generation (the step fuses them)",
                      "kernel_share_of_step": k32 / ms32,
                      "flops_per_point": f32,
                      "frac_of_nonpacked_fma": ach32 / NONPACKED_FMA_TFLOPS,

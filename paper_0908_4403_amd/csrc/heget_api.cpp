@@ -781,12 +781,17 @@ struct HistReq {
     double *host;  // [nbins + 2], pinned, written by the last kernel
 };
 
-// Whether a cross section runs as one fused kernel (the reasons stand in mc_fused.hip): not with a chosen kernel shape, or when
-// the amplitude kernel is to be timed.
+// Whether a cross section runs as one fused kernel (the reasons stand in
+// mc_fused.hip): not when the amplitude kernel is to be timed, or with a chosen
+// kernel shape other than the first of the list, whose walk the fused kernel runs
+// (the autotuner mostly chooses that one, and would otherwise cost the n = 4
+// cross section of 2^20 points 2%).
 bool runs_fused(int n, const heget_config &c)
 {
     const bool sampled = c.helicity_sampling != 0;
-    return heget::has_fused(n, c.prec, sampled, c.npoints) && !g.timing && (sampled || !g_tuned[c.prec][n]);
+    const heget::Me2Variant *chosen = g_tuned[c.prec][n];
+    return heget::has_fused(n, c.prec, sampled, c.npoints) && !g.timing &&
+           (sampled || !chosen || chosen == heget::me2_default(c.prec, n));
 }
 
 // The fused path into b.res, the result record and the pinned result; each
