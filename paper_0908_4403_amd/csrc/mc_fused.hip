@@ -11,6 +11,8 @@
 // -> 12.5 and 352 -> 200; n = 4 23 -> 17 and 519 -> 488 (1 048 576 points at
 // sqrt(shat) = 700 GeV 137 -> 130; pp, where a third is cut, 135 -> 138);
 // sampled n = 4 424 -> 246, n = 5 1 048 576 points 130 -> 120 (FP64 152 -> 141).
+// With the generation's tables since: n = 2, 4 194 304 points 108, n = 4, 1 048 576
+// points 125; sampled n = 5 111 (FP64 135).
 // Bound by VALU issue of FP64 and integer instructions, as gen_kernel.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -24,10 +26,9 @@ namespace heget {
 
 // Points up to which the FP64 n = 4 sum runs fused: its walk of sixteen
 // configurations leaves one wave per SIMD, which the generation in the same
-// kernel then has too (300 007 points 78 -> 62 us, 399 999 87 -> 79, 1e6 159 ->
-// 181).
+// kernel then has too (300 007 points 81 apart, 73 fused, 399 999 96 and 90,
+// 500 003 106 and 104, 600 003 115 and 121, 1e6 160 and 185).
 constexpr int64_t kFusedWide = 400000;
-
 
 // partials[3 b ..]: (sum, compensation, sum of squares) of block b's 256
 // weights; block_acc[b]: its accepted points, kBlockNonfinite added if one of
@@ -35,7 +36,7 @@ constexpr int64_t kFusedWide = 400000;
 // walk (unrolled n, closing, meeting in the middle) is that of the amplitude
 // kernel's default, so that a point keeps its bits.
 // FP64 n = 5 is held to two waves per SIMD: a few spills cost less than the
-// generation at one (300 007 points 62 -> 52 us); n = 4 with sixteen walks is
+// generation at one (300 007 points 62 -> 52 us, 49 with its tables); n = 4 with sixteen walks is
 // not (62 -> 80 us).
 template <typename R, int N, int MODE, int H>
 __global__ void __launch_bounds__(256)

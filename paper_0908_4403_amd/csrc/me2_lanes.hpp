@@ -37,7 +37,7 @@
 // u end's lanes read swapped copies of the blocks and a propagator of unity.
 // All LDS addresses of a lane come from tables made at compile time.
 //
-// What bounds it: in FP32 VALU issue (n = 8: 6 900 instructions per point; at
+// What bounds it: in FP32 VALU issue (n = 8: 7 000 instructions per point; at
 // four waves per SIMD the counters show the issue slots full, LDS busy half of
 // the clocks), in FP64 the LDS reads, 16 bytes each and two per value, of two
 // waves per SIMD (40 KiB of LDS per workgroup; more waves through a shared

@@ -150,7 +150,7 @@ def read_traffic(md_path: str, kernel: str):
 
 
 PROBE_KERNEL = "fma_peak_kernel<float>"
-ISSUE_KERNELS = ("me2_kernel", "gen_kernel", "compact_kernel", "final_kernel", "fma_peak_kernel")
+ISSUE_KERNELS = ("me2_kernel", "pairs::me2_pair_kernel", "lanes::me2_lanes_kernel", "fused_kernel", "gen_kernel", "compact_kernel", "final_kernel", "fma_peak_kernel")
 
 
 def issue(pmc_dirs):
