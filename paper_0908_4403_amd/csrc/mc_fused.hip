@@ -36,8 +36,8 @@ constexpr int64_t kFusedWide = 400000;
 // walk (unrolled n, closing, meeting in the middle) is that of the amplitude
 // kernel's default, so that a point keeps its bits.
 // FP64 n = 5 is held to two waves per SIMD: a few spills cost less than the
-// generation at one (300 007 points 62 -> 52 us, 49 with its tables); n = 4 with sixteen walks is
-// not (62 -> 80 us).
+// generation at one (300 007 points 62 -> 52 us, 49 with its tables); n = 4 with
+// sixteen walks is not (62 -> 80 us).
 template <typename R, int N, int MODE, int H>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(N == 5 && std::is_same<R, double>::value ? 2 : 1)))
