@@ -14,13 +14,13 @@
 // a point's work, with 16 instead of 32 FP64 accumulators and two thirds of the
 // values, and a wave holds 32 points: it walks a tile of 64 in two halves.
 //
-// What bounds it: in FP32 VALU issue at two waves per SIMD, 2 x 5950 instructions
+// What bounds it: in FP32 VALU issue at two waves per SIMD, 2 x 5760 instructions
 // per tile (the walk of all 32 configurations in a lane had 12 070, an eighth of
 // them moves to and from the upper half of its 512 registers, 96 KB of code, and
 // one wave per SIMD that waited a tenth of its time); in FP64 registers (one wave,
-// 100 spills).  Measured, us, before -> this: FP32 (that walk) 100 000 points 51 ->
-// 50, 300 000 124 -> 111, 1e6 368 -> 330, 2.4e6 858 -> 779; FP64 (eight per walk)
-// 65 536 points 68 -> 50, 1e6 923 -> 665, 2.4e6 2203 -> 1630.  Loading the next
+// 90 spills).  Measured, us, before -> this: FP32 (that walk) 100 000 points 51 ->
+// 49, 300 000 124 -> 107, 1e6 368 -> 312, 2.4e6 858 -> 734; FP64 (eight per walk)
+// 65 536 points 68 -> 46, 1e6 923 -> 634, 2.4e6 2203 -> 1540.  Loading the next
 // half tile ahead, by registers or through LDS, costs more instructions than it
 // hides waits (FP32 1e6 points 348 and 362 us); n = 4 (FP64) loses: its set-up and
 // propagators, which both lanes need, are a third of it (1e6 points 116 -> 149).
@@ -190,8 +190,12 @@ __device__ __forceinline__ double pair_sum(const Point<R, N> &s)
     double re[C], im[C];
 #pragma unroll
     for (int h = 0; h < C; ++h) re[h] = im[h] = 0.0;
-    for_each_subset<N, K>([&](auto ai) {
-        constexpr uint32_t A = decltype(ai)::value, B = kAll & ~A;
+    // From the highest set down: the sets with the last photon come first, so that the
+    // currents only they read are dead for the rest and fewer registers spill (FP32 53
+    // -> 35, FP64 110 -> 94 at n = 5; from the lowest up FP32 1e6 points 345 us, 312 so).
+    constexpr int kSets = binomial(N, K);
+    static_for<0, kSets>([&](auto si) {
+        constexpr uint32_t A = nth_subset(K, kSets - 1 - decltype(si)::value), B = kAll & ~A;
         Quad<R> j[MJ], w[MW];
         vertices<A, false, R, N, MJ>(s, J, j);
         const Quad<R> P = propagator<1, A>(s.q0, s);
