@@ -444,9 +444,12 @@ hist_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restric
         for (int c = 1; c < copies; ++c) v += lb[c * slots + b];
         if (v) __hip_atomic_fetch_add(&bins[b], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // the barrier orders the block's additions before thread 0's, whose release
-    // publishes them (a fence by every thread took 20 us: each one writes back
-    // the L2)
+    // Every wave waits until its own additions are done, then the barrier, then
+    // thread 0 counts the workgroup in.  Neither of the two waits for them: the
+    // barrier waits for no memory operation and thread 0's release for those of
+    // its own wave.  (A fence by every thread took 20 us: each one writes back
+    // the L2; the additions are done at memory and leave nothing in it.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0)
         last = __hip_atomic_fetch_add(&bins[slots], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
