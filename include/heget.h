@@ -243,11 +243,12 @@ heget_status heget_batch_schedule_in_use(const int *n, const heget_config *cfgs,
 /* Couplings used by heget_me2 / heget_me2_device (defaults: 1/137, 2/3). */
 heget_status heget_set_couplings(double alpha, double charge);
 
-/* Optional per-kernel timing of the amplitude kernel: when enabled, it runs as
- * a kernel of its own (short cross sections otherwise run as one kernel) and
- * each launch of it is bracketed by events on its stream; heget_timing_read
+/* Optional per-kernel timing of the amplitude kernel: when enabled, each
+ * launch of it is bracketed by events on its stream; heget_timing_read
  * returns the accumulated milliseconds and launch count since the last
- * reset (it synchronises the recorded events). */
+ * reset (it synchronises the recorded events).  No result depends on it: a
+ * cross section that runs as one kernel launches the amplitude kernel once
+ * more by itself, for its time alone (the call takes that much longer). */
 heget_status heget_timing_enable(int on);
 heget_status heget_timing_read(double *me2_ms, int64_t *me2_launches, int reset);
 

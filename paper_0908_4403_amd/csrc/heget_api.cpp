@@ -782,16 +782,25 @@ struct HistReq {
 };
 
 // Whether a cross section runs as one fused kernel (the reasons stand in
-// mc_fused.hip): not when the amplitude kernel is to be timed, or with a chosen
-// kernel shape other than the first of the list, whose walk the fused kernel runs
-// (the autotuner mostly chooses that one, and would otherwise cost the n = 4
-// cross section of 2^20 points 2%).
+// mc_fused.hip): not with a chosen kernel shape other than the first of the list,
+// whose walk the fused kernel runs (the autotuner mostly chooses that one, and
+// would otherwise cost the n = 4 cross section of 2^20 points 2%).
 bool runs_fused(int n, const heget_config &c)
 {
     const bool sampled = c.helicity_sampling != 0;
     const heget::Me2Variant *chosen = g_tuned[c.prec][n];
-    return heget::has_fused(n, c.prec, sampled, c.npoints) && !g.timing &&
+    return heget::has_fused(n, c.prec, sampled, c.npoints) &&
            (sampled || !chosen || chosen == heget::me2_default(c.prec, n));
+}
+
+// The amplitude kernel of a fused configuration by itself, for its time alone
+// (heget_timing_enable): the result stays that of the fused kernel, to the bit.
+heget_status time_amplitude(int n, const heget_config &c, const heget::Me2Variant &v, McBufs b, unsigned *flags,
+                            hipStream_t s)
+{
+    b.wout = nullptr;
+    HG_TRY(enqueue_generation(n, c, b, s, flags));
+    return launch_me2_timed(v, mc_me2_args(n, c, b, flags), s);
 }
 
 // The fused path into b.res, the result record and the pinned result; each
@@ -837,13 +846,14 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     b.nchunks = sampled ? 1 : plan_chunks(*v, np / 2);
     b.apart = sums_apart(*v, b.nchunks);
     const bool fused = runs_fused(n, *cfg);
-    b.beam = !fused && !hist && !ev && v->beam_func;
-    const size_t keep = fused ? 0 : size_t(np);  // points whose data goes through memory
+    b.beam = v->beam_func && (fused || (!hist && !ev));
+    const bool rows = !fused || g.timing;  // points go from kernel to kernel through memory
+    const size_t keep = rows ? size_t(np) : 0;
     unsigned *flags;
     HG_TRY(scratch_bind(s));
     // a fused histogram keeps each point's observable in place of its momenta
     const bool events_mom = ev && ev->momenta_soa;
-    HG_TRY(scratch_t<double>(S_MOM, fused && hist ? size_t(np) : size_t(n + 2) * 4 * (events_mom ? size_t(np) : keep),
+    HG_TRY(scratch_t<double>(S_MOM, !rows && hist ? size_t(np) : size_t(n + 2) * 4 * (events_mom ? size_t(np) : keep),
                              &b.mom));
     HG_TRY(scratch_t<double>(S_WFAC, events_mom ? size_t(np) : keep, &b.wfac));
     HG_TRY(scratch_t<uint8_t>(S_FLAG, keep, &b.flag));
@@ -873,6 +883,7 @@ heget_status xsec_enqueue(int n, const heget_config *cfg, heget_result *out, heg
     double *staged = d_out ? nullptr : g.pinned + kStaged * (g.ring.fetch_add(1) % kRing);
     if (staged_out) *staged_out = staged;
     if (fused) {
+        if (g.timing) HG_TRY(time_amplitude(n, *cfg, *v, b, flags, s));
         if (ev) HG_HIP(heget::launch_events(n, slice_gen_params(n, *cfg), ev_w, ev_y, ev_h, s));
         HG_TRY(enqueue_fused(n, *cfg, b, d_out, staged, s, ev ? ev_w : b.wout, hist, b.mom, bins));
         if (events_mom)  // the same points again, for their momenta
