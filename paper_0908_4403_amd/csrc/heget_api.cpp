@@ -1048,10 +1048,17 @@ heget_status batch_enqueue(int ncfg, const int *n, const heget_config *cfgs, Sli
     return HEGET_OK;
 }
 
+// What a captured batch was made for: the configurations, and the kernels that
+// they run now (heget_set_kernel_shape and heget_autotune change them; the fused
+// kernel runs with the first shape of the list, so the shape says that as well).
 std::string batch_key(int ncfg, const int *n, const heget_config *cfgs)
 {
     std::string k(reinterpret_cast<const char *>(n), sizeof(int) * size_t(ncfg));
     k.append(reinterpret_cast<const char *>(cfgs), sizeof(heget_config) * size_t(ncfg));
+    for (int i = 0; i < ncfg; ++i) {
+        const heget::Me2Variant *v = pick_variant(cfgs[i].prec, n[i], cfgs[i].npoints / 2);
+        k.append(reinterpret_cast<const char *>(&v), sizeof v);
+    }
     return k;
 }
 
