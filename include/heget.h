@@ -328,7 +328,9 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
  * device, and makes the fastest the shape every later call uses for (n,
  * prec) in this process (a shape later in the table must be 2% faster than
  * the best so far to replace it, so near-ties resolve the same way on every
- * run).  If HEGET_TUNING_CACHE names a file, the choice is
+ * run).  Where that is a kernel without helicity chunks (prefix_sets 2 with 32
+ * helicities per walk, or 6, at n = 5), calls of at most 32768 points and fewer
+ * than npoints run the walk in chunks that they run untuned.  If HEGET_TUNING_CACHE names a file, the choice is
  * also written there (one JSON object per line) and read back by later
  * processes on first device use.  *chosen and *ms (may be NULL) receive the
  * chosen shape and its time per launch.  64 <= npoints < 2^31. */

@@ -315,6 +315,7 @@ int plan_chunks(const heget::Me2Variant &v, int64_t points_expected)
 
 // Shape chosen by the autotuner (or loaded from the tuning cache) per (prec, n).
 const heget::Me2Variant *g_tuned[2][9] = {};
+int64_t g_measured[2][9] = {};  // points of the autotuner's calls that chose it (0: set by the caller)
 
 const heget::Me2Variant *find_variant(int prec, int n, int mb, int h, int cl, int wpb, int pf, int wpe,
                                       int ppl, int ps);
@@ -345,10 +346,23 @@ const heget::Me2Variant *default_variant(int prec, int n, int64_t points)
     return all ? all : heget::me2_default(prec, n);
 }
 
+bool is_shared(const heget::Me2Variant *v)
+{
+    for (int i = 0; const heget::Me2Variant *all = heget::me2_shared(v->prec, v->n, i); ++i)
+        if (v == all) return true;
+    return false;
+}
+
+// The kernels that form every current once have no helicity chunks: where the
+// autotuner chose one of them (n = 5), calls of fewer points than it measured keep
+// the walk that splits where they run it without tuning (500 points 14 us, 23 in
+// the chosen one).  A shape set by the caller runs at every size.
 const heget::Me2Variant *pick_variant(int prec, int n, int64_t points)
 {
-    if (prec >= 0 && prec < 2 && n >= 2 && n <= 8 && g_tuned[prec][n]) return g_tuned[prec][n];
-    return default_variant(prec, n, points);
+    const heget::Me2Variant *def = default_variant(prec, n, points);
+    if (prec < 0 || prec > 1 || n < 2 || n > 8 || !g_tuned[prec][n]) return def;
+    const heget::Me2Variant *chosen = g_tuned[prec][n];
+    return points < g_measured[prec][n] && is_shared(chosen) && !is_shared(def) ? def : chosen;
 }
 
 // The amplitude kernel writes |M|^2 per point and the weighted sums follow in
@@ -393,7 +407,11 @@ void load_tuning_cache()
                         arch, &prec, &n, &mb, &h, &cl, &wpb, &pf, &wpe, &ppl, &ps) == 11 &&
             g_arch == arch && prec >= 0 && prec < 2 && n >= 2 && n <= 8) {
             const heget::Me2Variant *v = find_variant(prec, n, mb, h, cl, wpb, pf, wpe, ppl, ps);
-            if (v) g_tuned[prec][n] = v;
+            if (v) {
+                g_tuned[prec][n] = v;
+                const char *at = std::strstr(line, "\"points\": ");
+                g_measured[prec][n] = at ? std::atoll(at + 10) : 0;
+            }
         }
     }
     std::fclose(f);
@@ -1750,6 +1768,7 @@ heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape
     (void)hipEventDestroy(e1);
     if (!best) return fail(HEGET_ERR_ARG, "no compiled amplitude kernel for this n/precision");
     g_tuned[prec][n] = best;
+    g_measured[prec][n] = npoints;
     save_tuning_cache(*best, best_ms, npoints);
     if (chosen) *chosen = shape_of(*best);
     if (ms) *ms = best_ms;
@@ -1763,6 +1782,7 @@ heget_status heget_set_kernel_shape(int n, heget_prec prec, const heget_shape *s
     HG_TRY(check_prec(prec));
     std::lock_guard<std::mutex> lk(g_mu);
     if (!shape) {
+        g_measured[prec][n] = 0;
         g_tuned[prec][n] = nullptr;
         return HEGET_OK;
     }
@@ -1772,6 +1792,7 @@ heget_status heget_set_kernel_shape(int n, heget_prec prec, const heget_shape *s
                      shape->points_per_lane, shape->prefix_sets);
     if (!v) return fail(HEGET_ERR_ARG, "no compiled kernel shape with these parameters");
     g_tuned[prec][n] = v;
+    g_measured[prec][n] = 0;
     return HEGET_OK;
 }
 
