@@ -332,7 +332,8 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
  * helicities per walk, or 6, at n = 5), calls of at most 32768 points and fewer
  * than npoints run the walk in chunks that they run untuned.  If HEGET_TUNING_CACHE names a file, the choice is
  * also written there (one JSON object per line) and read back by later
- * processes on first device use.  *chosen and *ms (may be NULL) receive the
+ * processes on first device use; a line written by a library that did not have
+ * the kernels of prefix_sets 5 and 6 is not used for the n that have them.  *chosen and *ms (may be NULL) receive the
  * chosen shape and its time per launch.  64 <= npoints < 2^31. */
 heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape *chosen,
                             double *ms);

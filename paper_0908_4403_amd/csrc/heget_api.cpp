@@ -392,7 +392,17 @@ heget_shape shape_of(const heget::Me2Variant &v)
 
 // Tuning cache: one JSON object per line,
 // {"arch": "gfx950", "prec": 1, "n": 4, "mb": 4, "h": 2, "cl": 2, "wpb": 4, "pf": 0, "wpe": 2,
-//  "ppl": 1, "ps": 0, "ms": 0.48, "points": 1048576}
+//  "ppl": 1, "ps": 0, "ms": 0.48, "points": 1048576, "shared": 0}
+// "shared" counts the kernels beside the list (me2_shared) that were tried too; a
+// line without it tried none.  A choice made without the kernels that there are
+// now is left for the default (it would pin n = 8 to a walk 13 times slower).
+int shared_count(int prec, int n)
+{
+    int k = 0;
+    while (heget::me2_shared(prec, n, k)) ++k;
+    return k;
+}
+
 void load_tuning_cache()
 {
     const char *path = std::getenv("HEGET_TUNING_CACHE");
@@ -407,9 +417,9 @@ void load_tuning_cache()
                         arch, &prec, &n, &mb, &h, &cl, &wpb, &pf, &wpe, &ppl, &ps) == 11 &&
             g_arch == arch && prec >= 0 && prec < 2 && n >= 2 && n <= 8) {
             const heget::Me2Variant *v = find_variant(prec, n, mb, h, cl, wpb, pf, wpe, ppl, ps);
-            if (v) {
+            const char *at = std::strstr(line, "\"points\": "), *tried = std::strstr(line, "\"shared\": ");
+            if (v && (tried ? std::atoi(tried + 10) : 0) == shared_count(prec, n)) {
                 g_tuned[prec][n] = v;
-                const char *at = std::strstr(line, "\"points\": ");
                 g_measured[prec][n] = at ? std::atoll(at + 10) : 0;
             }
         }
@@ -433,9 +443,9 @@ void save_tuning_cache(const heget::Me2Variant &v, double ms, int64_t points)
     }
     if (FILE *f = std::fopen(path, "w")) {
         for (const std::string &l : keep) std::fputs(l.c_str(), f);
-        std::fprintf(f, "{\"arch\": \"%s\", \"prec\": %d, \"n\": %d, \"mb\": %d, \"h\": %d, \"cl\": %d, \"wpb\": %d, \"pf\": %d, \"wpe\": %d, \"ppl\": %d, \"ps\": %d, \"ms\": %.6f, \"points\": %lld}\n",
+        std::fprintf(f, "{\"arch\": \"%s\", \"prec\": %d, \"n\": %d, \"mb\": %d, \"h\": %d, \"cl\": %d, \"wpb\": %d, \"pf\": %d, \"wpe\": %d, \"ppl\": %d, \"ps\": %d, \"ms\": %.6f, \"points\": %lld, \"shared\": %d}\n",
                      g_arch.c_str(), v.prec, v.n, v.mb, v.h, v.cl, v.wpb, v.pf, v.wpe, v.ppl, v.ps, ms,
-                     static_cast<long long>(points));
+                     static_cast<long long>(points), shared_count(v.prec, v.n));
         std::fclose(f);
     }
 }
