@@ -320,7 +320,8 @@ typedef struct {
  * = 1, counted on the schedule actually executed (the 2^n helicities of one
  * quark-helicity block; the shape's tree, closing and helicity sharing).
  * Per-point O(n) set-up is not counted.  *shape (may be NULL) receives the
- * shape in use. */
+ * shape in use; at n = 5 without a chosen shape, where it depends on the size of
+ * the call, that of the largest calls. */
 heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, heget_shape *shape);
 
 /* Autotuner.  Times every compiled shape of the amplitude kernel for (n,
@@ -338,13 +339,16 @@ heget_status heget_me2_flops(int n, heget_prec prec, double *flops_per_point, he
 heget_status heget_autotune(int n, heget_prec prec, int64_t npoints, heget_shape *chosen,
                             double *ms);
 
-/* The compiled walk shapes for (n, prec), the one in use first, into shapes[i]
- * for i < max (shapes may be NULL when max = 0); *count receives how many
- * exist.  The kernels that form every subset current once per point
- * (helicities_per_walk = 2^n; the defaults for n >= 6 and for n = 5 FP32) are
- * not among them: heget_me2_flops names them where they are in use, and
- * heget_set_kernel_shape takes their shapes.  Without a chosen shape n = 5
- * calls of up to 32768 points run a walk of fewer helicities. */
+/* The compiled walk shapes for (n, prec) into shapes[i] for i < max (shapes may
+ * be NULL when max = 0), the chosen one (heget_set_kernel_shape, the autotuner)
+ * first; *count receives how many there are.  Without a chosen shape n = 2 to 4
+ * run the first of them.  n >= 5 then run kernels that form every subset current
+ * once per point (helicities_per_walk = 2^n), which the list holds only where one
+ * is chosen: n >= 6 those of prefix_sets 5 at every size; n = 5 those of
+ * prefix_sets 6, in FP32 from 65537 points on and below that a walk of all 32
+ * configurations, and calls of up to 32768 points a shape of the list with fewer
+ * helicities per walk.  heget_me2_flops names the kernel of the large calls, and
+ * heget_set_kernel_shape takes its shape. */
 heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *shapes, int *count);
 
 /* Use a compiled shape for (n, prec) from now on in this process; NULL

@@ -1814,10 +1814,9 @@ heget_status heget_kernel_shapes(int n, heget_prec prec, int max, heget_shape *s
     if (!count || (max > 0 && !shapes)) return fail(HEGET_ERR_ARG, "null pointer");
     int cnt = 0, k = 0;
     const heget::Me2Variant *all = heget::me2_variants(&cnt);
-    const heget::Me2Variant *cur = pick_variant(prec, n, kMaxPoints);
-    for (int i = 0; const heget::Me2Variant *all = heget::me2_shared(prec, n, i); ++i)
-        if (cur == all) cur = heget::me2_default(prec, n);  // not in the list
-    if (cur) {  // the shape in use first
+    // the chosen shape first, also where it is not in the list
+    const heget::Me2Variant *cur = g_tuned[prec][n] ? g_tuned[prec][n] : heget::me2_default(prec, n);
+    if (cur) {
         if (k < max) shapes[k] = shape_of(*cur);
         ++k;
     }
