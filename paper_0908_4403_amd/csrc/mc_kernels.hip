@@ -528,7 +528,8 @@ hipError_t launch_compact(int32_t *counts, const uint8_t *flag, int64_t np, int3
                           int64_t *d_count, hipStream_t stream)
 {
     const int64_t blocks = (np + 255) / 256;
-    if (blocks == 0) return hipSuccess;
+    // no points (an empty configuration of a batch): what follows reads the count all the same
+    if (blocks == 0) return launch_zero_u32(reinterpret_cast<unsigned *>(d_count), 2, stream);
     const int scanned = blocks > kScanAboveBlocks ? 1 : 0;
     if (scanned)
         hipLaunchKernelGGL(block_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, counts,
