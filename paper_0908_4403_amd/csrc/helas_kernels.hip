@@ -145,11 +145,11 @@ __global__ __launch_bounds__(64 * W) void me2_frame_kernel(const double *__restr
     const int64_t c = i < np ? i : np - 1;  // lanes past the last point repeat it and store nothing
     int ex = 0;
     frexp(mom[c] + mom[4 * ld + c], &ex);
-    const double sc = ldexp(1.0, -ex);
+    // scaled by ldexp: 2^-ex itself overflows for energies below 2^-1024
     auto load = [&](int particle) {
         double p[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) p[m] = mom[(4 * particle + m) * ld + c] * sc;
+        for (int m = 0; m < 4; ++m) p[m] = ldexp(mom[(4 * particle + m) * ld + c], -ex);
         return spinor(p);
     };
     const Spinor l1 = load(0), l2 = load(1);
