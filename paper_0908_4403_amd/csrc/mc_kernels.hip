@@ -396,34 +396,48 @@ __device__ __forceinline__ void hist_add(unsigned long long *lb, double x, doubl
 
 // The histogram of the survivors' observable (N photons from mom through
 // index, or N = 0: x and w per generated point, as the fused pass writes them).
-// At most kHistBlocks workgroups: every one adds each of its bins to the same
+// At most 128 workgroups (kHistBlocks): every one adds each of its bins to the same
 // words in memory, one after the other (some 20 ns each).  The last one to
 // finish (bins[nbins + 2] counts them) converts the sums to sum(w) / n_gen per
 // bin into `hist`.  300 007 sampled n = 5 points, of which the fused pass left
 // weight and observable: 7 us; 23 us when a workgroup of 256 took every 256
 // survivors from their momenta, and 10 more for the conversion and the zeroing
 // of the bins in kernels of their own.
-constexpr int kHistBlocks = 128, kHistThreads = 1024;
+//
+// Delta R of gathered survivors is work (n logarithms, arctangents, n (n - 1) / 2
+// roots): a workgroup for each CU, and from n = 6 half as many threads, which 128
+// registers are too few for.  us, one kernel per 256 survivors -> 128 workgroups of
+// 1024 -> this: pp n = 5 of 4.2e6 points 138 -> 217 -> 138, n = 5 of 1e6 57 -> 69 ->
+// 44, FP64 n = 4 of 1e6 54 -> 59 -> 42, sampled n = 6, 7, 8 of 1e6 58 -> 75 -> 49, 59 -> 89
+// -> 54, 59 -> 103 -> 58; n = 8 of 65 536 17 -> 31 -> 16.  The largest pT gains nothing by
+// either (n = 5 of 1e6 22 and 22, FP64 n = 4 18 and 21).
+template <int N, int WHICH>
+constexpr bool kHistWork = N > 0 && WHICH == 1;
+template <int N, int WHICH>
+constexpr int kHistBlocks = kHistWork<N, WHICH> ? 256 : 128;
+template <int N, int WHICH>
+constexpr int kHistThreads = kHistWork<N, WHICH> && N >= 6 ? 512 : 1024;
 
 template <int N, int WHICH>
-__global__ void __launch_bounds__(kHistThreads)
+__global__ void __launch_bounds__((kHistThreads<N, WHICH>))
 hist_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restrict__ index,
             const double *__restrict__ w, const int64_t *__restrict__ d_count, int64_t points,
             const double *__restrict__ res, int nbins, double lo, double hi, unsigned long long *bins,
             int64_t n_gen, double *__restrict__ hist)
 {
+    constexpr int kThreads = kHistThreads<N, WHICH>;
     __shared__ unsigned long long lb[kHistSlots];
     __shared__ int last;
     const int slots = nbins + 2;
     const int copies = slots * 4 <= kHistSlots ? 4 : 1;
-    for (int b = threadIdx.x; b < slots * copies; b += kHistThreads) lb[b] = 0ull;
+    for (int b = threadIdx.x; b < slots * copies; b += kThreads) lb[b] = 0ull;
     __syncthreads();
     unsigned long long *mine = lb + (copies == 4 ? (threadIdx.x >> 6 & 3) * slots : 0);
     const int64_t count = N == 0 ? points : *d_count;
     const int shift = hist_shift(res);
     const double scale = static_cast<double>(nbins) / (hi - lo);
-    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kHistThreads + threadIdx.x; k < count;
-         k += static_cast<int64_t>(gridDim.x) * kHistThreads) {
+    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; k < count;
+         k += static_cast<int64_t>(gridDim.x) * kThreads) {
         double x;
         if constexpr (N == 0) {
             x = mom[k];
@@ -439,7 +453,7 @@ hist_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restric
         hist_add(mine, x, w[k], shift, nbins, lo, hi, scale);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < slots; b += kHistThreads) {
+    for (int b = threadIdx.x; b < slots; b += kThreads) {
         unsigned long long v = lb[b];
         for (int c = 1; c < copies; ++c) v += lb[c * slots + b];
         if (v) __hip_atomic_fetch_add(&bins[b], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -456,7 +470,7 @@ hist_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__restric
                gridDim.x - 1u;
     __syncthreads();
     if (!last) return;
-    for (int b = threadIdx.x; b < slots; b += kHistThreads) {
+    for (int b = threadIdx.x; b < slots; b += kThreads) {
         const unsigned long long v = __hip_atomic_load(&bins[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         hist[b] = n_gen > 0 ? ldexp(static_cast<double>(v), -shift) / static_cast<double>(n_gen) : 0.0;
     }
@@ -561,9 +575,10 @@ hipError_t launch_final(const double *partials, const int64_t *d_count, const in
 template <int N, int WHICH>
 static hipError_t hist_nw(const HistArgs &a, hipStream_t stream)
 {
-    int64_t blocks = (a.points + kHistThreads - 1) / kHistThreads;
-    blocks = blocks < 1 ? 1 : (blocks > kHistBlocks ? kHistBlocks : blocks);
-    hipLaunchKernelGGL((hist_kernel<N, WHICH>), dim3(static_cast<unsigned>(blocks)), dim3(kHistThreads), 0, stream,
+    constexpr int kThreads = kHistThreads<N, WHICH>;
+    int64_t blocks = (a.points + kThreads - 1) / kThreads;
+    blocks = blocks < 1 ? 1 : (blocks > kHistBlocks<N, WHICH> ? kHistBlocks<N, WHICH> : blocks);
+    hipLaunchKernelGGL((hist_kernel<N, WHICH>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, stream,
                        a.mom, a.ld, a.index, a.w, a.d_count, a.points, a.res, a.nbins, a.lo, a.hi, a.bins, a.n_gen,
                        a.hist);
     return hipGetLastError();
