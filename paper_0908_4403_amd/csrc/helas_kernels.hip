@@ -125,9 +125,9 @@ __device__ inline Cx<double> product(const Spinor &p, const Spinor &q)
 // shortens the walk of a wave where tiles are few.
 // Bound by VALU issue from some 1e5 points on, below that by one wave's
 // latency.  Time, with the chains over all orderings of 4-spinors for both
-// quark helicities that this replaces -> now: 20 011 points n = 4 FP64 563 ->
-// 13.5 us, n = 5 FP64 5570 -> 48 us, n = 5 FP32 5150 -> 27 us; 200 003 points
-// n = 3 FP64 161 -> 17 us, n = 4 FP32 1040 -> 33 us, n = 5 FP64 22.5 -> 0.23
+// quark helicities that this replaces -> now: 20 011 points n = 4 FP64 564 ->
+// 9.9 us, n = 5 FP64 5600 -> 37 us, n = 5 FP32 5160 -> 25 us; 200 003 points
+// n = 3 FP64 159 -> 18 us, n = 4 FP32 997 -> 31 us, n = 5 FP64 22.5 -> 0.21
 // ms; n = 2 is bound by the launch on both.  Errors against 64-bit values are
 // no larger (median at n = 4 2.2e-15 -> 2.0e-15 in FP64, 7.9e-7 -> 1.1e-7 in
 // FP32; at a boost of gamma = 20 1.5e-12 -> 9e-15 and 8e-4 -> 1.1e-7).
@@ -185,9 +185,15 @@ __global__ __launch_bounds__(64 * W) void me2_frame_kernel(const double *__restr
     if (!isfinite(r)) atomicOr(flags, 1u);
 }
 
-// Tiles below which the walks of a point are split over four waves: two waves
-// per SIMD on 256 CUs hold 2048 tiles at once.
-constexpr int64_t kFrameSplitTiles = 2048;
+// Tiles up to which the walks of a point are split over four waves.  Four waves a
+// tile fill the 1024 SIMDs of 256 CUs at 256 tiles, and at one wave per SIMD (278 to
+// 498 registers in FP64, 372 in FP32 at n = 5) any more wait for a second round: at
+// n = 4 that is longer than the undivided walk, at n = 5 two rounds are still shorter.
+// us, four waves and one: n = 4 FP64 16 384 points 8.2 and 9.7, 20 011 12.8 and 9.9,
+// 131 072 45 and 19; FP32 16 384 8.8 and 9.4, 20 011 10.7 and 9.6; n = 5 FP64 16 384 21
+// and 47, 32 768 40 and 52, 65 536 75 and 61; FP32 32 768 26 and 30, 65 536 49 and 32.
+template <int N>
+constexpr int64_t kFrameSplitTiles = N >= 5 ? 512 : 256;
 
 template <typename R, int N, int H, int CL, int PS, int HS>
 hipError_t launch_frame_n(int64_t np, const double *mom, int64_t ld, double coef, double *out,
@@ -196,7 +202,7 @@ hipError_t launch_frame_n(int64_t np, const double *mom, int64_t ld, double coef
     const int64_t tiles = (np + 63) / 64;
     constexpr int W = (1 << N) / HS >= 4 ? 4 : 1;  // n = 2, 3 have too few walks to split
     if constexpr (W > 1) {
-        if (tiles < kFrameSplitTiles) {
+        if (tiles <= kFrameSplitTiles<N>) {
             hipLaunchKernelGGL((me2_frame_kernel<R, N, HS, CL, PS, W>), dim3(unsigned(tiles)), dim3(64 * W), 0, s,
                                mom, ld, np, coef, out, flags);
             return hipGetLastError();
