@@ -811,7 +811,7 @@ struct HistReq {
 
 // Whether a cross section runs as one fused kernel (the reasons stand in
 // mc_fused.hip): not with a chosen kernel shape other than the first of the list,
-// whose walk the fused kernel runs (the autotuner mostly chooses that one, and
+// whose part the fused kernel takes (the autotuner mostly chooses that one, and
 // would otherwise cost the n = 4 cross section of 2^20 points 2%).
 bool runs_fused(int n, const heget_config &c)
 {

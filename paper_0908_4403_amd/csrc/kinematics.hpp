@@ -247,17 +247,6 @@ __device__ __forceinline__ int screen_cuts(const Vec4 (&k)[N], double y, double 
     return unsure ? -1 : (ok ? 1 : 0);
 }
 
-// The cut decision: the FP32 screen, and the FP64 evaluation only for points
-// the screen leaves open.
-template <int N>
-__device__ __forceinline__ bool pass_cuts(const Vec4 (&k)[N], double y, double pt_min,
-                                          double eta_max, double dr_min)
-{
-    const int s = screen_cuts<N>(k, y, pt_min, eta_max, dr_min);
-    if (s >= 0) return s == 1;
-    return pass_cuts_fp64<N>(k, y, pt_min, eta_max, dr_min);
-}
-
 // Kinematic parameters shared by every point of one generation call.
 struct GenParams {
     int mode;            // heget_mode

@@ -34,7 +34,9 @@ constexpr int64_t kFusedWide = 400000;
 // weights; block_acc[b]: its accepted points, kBlockNonfinite added if one of
 // their weights is not finite.  H = 0: the drawn helicity configuration.  The
 // walk (unrolled n, closing, meeting in the middle) is that of the amplitude
-// kernel's default, so that a point keeps its bits.
+// kernel's default, but for n = 2 and FP64 n = 3 of all helicities at once, not half
+// of them.  FP32 and sampled points have the same bits in both; in FP64 sums the
+// compiler contracts products differently (up to 2e-14 of a point).
 // FP64 n = 5 is held to two waves per SIMD: a few spills cost less than the
 // generation at one (300 007 points 62 -> 52 us, 49 with its tables); n = 4 with
 // sixteen walks is not (62 -> 80 us).
