@@ -366,6 +366,19 @@ __device__ __forceinline__ double octet_product(double v)
     return v;
 }
 
+// Sum of v, |v| <= 1, over each eight lanes less `target`, which lies close to it, to
+// well below a rounding of v: the multiples of 2^-40 in v add exactly, and the rest
+// of it is that small.
+__device__ __forceinline__ double octet_excess(double v, double target)
+{
+    constexpr double kGrid = 0x1.8p+12;
+    double hi = (v + kGrid) - kGrid, lo = v - hi;
+    hi += dpp_f64<0xB1>(hi), lo += dpp_f64<0xB1>(lo);
+    hi += dpp_f64<0x4E>(hi), lo += dpp_f64<0x4E>(lo);
+    hi += dpp_f64<0x141>(hi), lo += dpp_f64<0x141>(lo);
+    return (hi - target) + lo;
+}
+
 // s (+)= V c for a current c = (g2, g3) (or c V for a row, ROW) with one
 // lane's vertex block v = (beta, gamma).
 template <bool ROW, bool FIRST, typename R>
@@ -419,10 +432,12 @@ __device__ __forceinline__ void vertices(const char *lds_all, const u32x4 &row, 
     });
 }
 
-// Propagators of the COUNT tasks from FIRST in the table on, to entry `AT`:
-// d (q-, q+, qx, qy) with q = base + sign * (sum of the task's photons).
-template <typename R, int N, int W, int FIRST, int COUNT, int AT, int PLANE>
-__device__ __forceinline__ void propagators(char *lds, int s, int first, R base_p, R base_m, R sign)
+// Propagators of the COUNT tasks from FIRST in the table on, to entry `AT`
+// (rest: where REST is set):
+// d (q-, q+, qx, qy) with q = base + sign * (sum of the task's photons) + rest.
+template <typename R, int N, int W, int FIRST, int COUNT, int AT, int PLANE, bool REST = false>
+__device__ __forceinline__ void propagators(char *lds, int s, int first, R base_p, R base_m, R sign,
+                                            const Quad<R> &rest = {})
 {
     using L = Split<N, W>;
     constexpr int S = L::S;
@@ -445,6 +460,7 @@ __device__ __forceinline__ void propagators(char *lds, int s, int first, R base_
             x = fma(sign, k.c, x);
             y = fma(sign, k.d, y);
         }
+        if constexpr (REST) p += rest.a, m += rest.b, x += rest.c, y += rest.d;
         const R q2 = p * m - x * x - y * y;
         const R d = neg_recip(q2);
         put<PLANE>(lds + (AT + t) * 16, Quad<R>{d * m, d * p, d * x, d * y});
@@ -636,7 +652,19 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         end = (x + 1) * per < nitems ? (x + 1) * per : nitems;
     }
     if (item >= end) return;
-    const int photon = s < N ? s : N - 1;
+    // The photons' momenta add up to p1 + p2 only to a rounding, and the u end
+    // starts from p1: at a soft set its momenta are then another event's than the
+    // v-bar end's by more than their own rounding.  Where one lane per point walked
+    // from the v-bar end alone (FP64 n = 8) the u end takes what is left over,
+    // rest = sum of the photons - p1 - p2, with every momentum.  Against the oracle's
+    // 1024 stored points, that walk -> p1 as it is -> with the rest: median 9.8e-15
+    // -> 1.15e-14 -> 7.8e-15, 99th percentile 1.36e-13 -> 1.54e-13 -> 9.1e-14, maximum
+    // 2.5e-13 -> 2.9e-13 -> 2.1e-13; 20 001 points 384.6 -> 386.6 us.  n = 6 and 7
+    // met in the middle before too, with the same errors as now.
+    constexpr bool kBalance = !kF32 && N == 8;
+    // (every eight lanes hold all photons where their sum is formed)
+    const int own = kBalance ? s & 7 : s;
+    const int photon = own < N ? own : N - 1;
     // loads past the last point repeat it (never stored)
     auto column = [&](int64_t it) -> uint32_t {
         const int64_t i = it * P + pt;
@@ -686,6 +714,12 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
             im_ = 1.0 / km;
         }
         const double norm_den = octet_product(s < N ? 2.0 * E * E / pt2 : 1.0);
+        Quad<R> rest{};
+        if constexpr (kBalance) {
+            const bool in = own < N;
+            rest = {octet_excess(in ? kp : 0.0, p1p - q0p), octet_excess(in ? km : 0.0, p1m - q0m),
+                    octet_excess(in ? kx : 0.0, 0.0), octet_excess(in ? ky : 0.0, 0.0)};
+        }
         if (wave == 0 && s < N) {
             const R fx = static_cast<R>(kx), fy = static_cast<R>(ky);
             const R xp = fx * ip, yp = fy * ip, xm = fx * im_, ym = fy * im_;
@@ -712,7 +746,7 @@ me2_lanes_kernel(const double *__restrict__ mom, int64_t ld, const int32_t *__re
         constexpr int kPj = L::props_j(), kPr = L::props_r();
         const int first = wave, other = W - 1 - wave;
         propagators<R, N, W, 0, kPj, L::kProp, PLANE>(lds, s, first, q0p, q0m, R(1));
-        propagators<R, N, W, kPj, kPr, L::kT2, PLANE>(lds, s, other, p1p, p1m, R(-1));
+        propagators<R, N, W, kPj, kPr, L::kT2, PLANE, kBalance>(lds, s, other, p1p, p1m, R(-1), rest);
         __syncthreads();
 
         // ---- phase 3
