@@ -293,17 +293,28 @@ double me2_flops_per_point(int n, int mb, int h, int cl, int ps = 0);
 // against 99 us in 8192 items); an item of fewer operations than kSplitFlops
 // takes less than that pass (n = 3 FP64, 1.5e5: 7.7 us whole, 10.4 in two), one
 // of more takes longer (n = 5 FP32, 1.7e6: 500 points 19 us whole, 14 in four).
-constexpr int64_t kFillItems = 1024;
-constexpr double kSplitFlops = 2e5;
+// One wave per SIMD is what the walks unrolled over all n photons hold.  Those
+// that keep the top levels outside (mb < n) hold two to four, and the waves of the
+// persistent batch kernel take items from a queue that evens out only over several
+// each: both are split up to kManyItems, down to items of kManyFlops.  us, by the rule
+// above -> so: n = 6 FP32 walks of four unrolled photons, 65 536 points 1384 -> 1036,
+// n = 7 16 384 points 1800 -> 1402; persistent batches FP32 n = 7 of 2^15 points 3221 ->
+// 1226, n = 8 of 2^14 4708 -> 2700, n = 2 .. 7 of 2^(22 - n) 3607 -> 2432 (n = 2 .. 4,
+// whose items are smaller, as before: 523 -> 519, and 630 split down to kSplitFlops).
+constexpr int64_t kFillItems = 1024, kManyItems = 8192;
+constexpr double kSplitFlops = 2e5, kManyFlops = 1e6;
 constexpr double kTailFlops = 2e8;
 
-int plan_chunks_shape(int n, int mb, int h, int cl, int ps, int64_t points_expected)
+int plan_chunks_shape(int n, int mb, int h, int cl, int ps, int64_t points_expected, bool persistent = false)
 {
     const int passes = (1 << n) / h;
     const int64_t tiles = (points_expected + 63) / 64;
     const double item_flops = 64.0 * me2_flops_per_point(n, mb, h, cl, ps);
+    const bool many = persistent || mb < n;
     int c = 1;
-    while (c < passes && ((tiles * 2 * c <= kFillItems && item_flops / c > kSplitFlops) || item_flops / c > kTailFlops))
+    while (c < passes &&
+           ((tiles * 2 * c <= kFillItems && item_flops / c > kSplitFlops) ||
+            (many && tiles * c < kManyItems && item_flops / c > kManyFlops) || item_flops / c > kTailFlops))
         c *= 2;
     return c;
 }
@@ -991,7 +1002,7 @@ void carve_batch(Arena &ar, int ncfg, const int *n, const heget_config *cfgs, in
             sl.ps = v->ps;
         }
         McBufs &b = sl.b;
-        b.nchunks = plan_chunks_shape(n[s], sl.mb, sl.h, sl.cl, sl.ps, np / 2);
+        b.nchunks = plan_chunks_shape(n[s], sl.mb, sl.h, sl.cl, sl.ps, np / 2, schedule == 1);
         b.mom = ar.take<double>(size_t(n[s] + 2) * 4 * size_t(np));
         b.wfac = ar.take<double>(size_t(np));
         b.flag = ar.take<uint8_t>(size_t(np));
