@@ -113,7 +113,7 @@ def run_steps(H, torch, n, cfg, steps, warmup, nstreams=1):
 
 def mixed_batch(H, torch, prec, steps):
     """n = 2..7 with 2^22..2^17 points, sqrt(shat) uniform in [200 GeV, 2 TeV]:
-    one heget_xsec_batch (persistent amplitude launch, graph-captured) against
+    one heget_xsec_batch (a replay of its graph) against
     one heget_xsec call per n."""
     _, mixed = _workloads()
     ns = [s["n"] for s in mixed]

@@ -46,7 +46,7 @@
 // to two waves -> this form; 131 101, 65 537 and 20 001 points): FP32 n = 6
 // 397 -> 191 -> 154, n = 7 1 530 -> 284 -> 243, n = 8 3 100 -> 249 -> 220; FP64
 // n = 6 1 350 -> 281 -> 272, n = 7 7 400 -> 447 -> 428, n = 8 16 700 -> 395 ->
-// 381.  At 2053 points FP32: n = 6 11.0 -> 8.4, n = 7 19.4 -> 14.6, n = 8 32.0 ->
+// 387.  At 2053 points FP32: n = 6 11.0 -> 8.4, n = 7 19.4 -> 14.6, n = 8 32.0 ->
 // 28.7.  Every FP32 value is formed by the same operations in the same order in
 // all of these, so FP32 results have the same bits (up to the order in which the
 // waves add the sets).
