@@ -380,7 +380,8 @@ SHAPE_FIELDS = ("unrolled", "helicities_per_walk", "closing", "waves_per_block",
 
 
 def me2_flops(n: int, prec: int = FP32):
-    """(algorithmic flops per point, shape tuple) of the kernel in use for (n, prec)."""
+    """(algorithmic flops per point, shape tuple) of the kernel in use for (n, prec);
+    where it depends on the size of the call (n = 5), of the largest calls."""
     f, s = C.c_double(), Shape()
     _check(_lib.heget_me2_flops(n, prec, C.byref(f), C.byref(s)), "heget_me2_flops")
     return f.value, s.as_tuple()
@@ -396,8 +397,8 @@ def autotune(n: int, prec: int = FP32, npoints: int = 1 << 18) -> dict:
 
 
 def kernel_shapes(n: int, prec: int = FP32):
-    """Compiled shapes for (n, prec) as tuples (unrolled, helicities_per_walk,
-    closing, waves_per_block, prefetch), the shape in use first."""
+    """Compiled walk shapes for (n, prec) as tuples of SHAPE_FIELDS, a chosen one first
+    (without one, n >= 5 runs kernels outside this list: see heget_kernel_shapes)."""
     cnt = C.c_int()
     _check(_lib.heget_kernel_shapes(n, prec, 0, None, C.byref(cnt)), "heget_kernel_shapes")
     arr = (Shape * cnt.value)()
@@ -516,7 +517,8 @@ def helas_device(func, records, out, prec: int = FP64, stream=None) -> None:
 
 
 def me2_frame(momenta, prec: int = FP64, return_status: bool = False):
-    """Helicity-summed |M|^2 of u ubar -> n photons (n <= 5) at momenta[npoints, n+2, 4] in any frame."""
+    """Helicity-summed |M|^2 of u ubar -> n photons (n <= 5) at momenta[npoints, n+2, 4] in any frame
+    (p1 + p2 = sum of the photons)."""
     p = np.ascontiguousarray(momenta, dtype=np.float64)
     if p.ndim != 3 or p.shape[2] != 4:
         raise ValueError("momenta must have shape [npoints, n+2, 4]")
